@@ -72,9 +72,9 @@
  *     across lanes (calls and items shorter than a few vectors take a slower
  *     scalar path with the same results).
  *     xred_ring_reduce refuses chunks at different offsets (see there);
- *     xred_reduce_copy_step, xred_acc_cast and
- *     xred_allreduce_sim take the vector path only when every buffer they
- *     touch is 16-byte aligned, else the scalar one.
+ *     xred_reduce_copy_step and xred_acc_cast run at one speed whatever the
+ *     buffers' alignment; xred_allreduce_sim takes the vector path only when
+ *     every buffer it touches is 16-byte aligned, else a scalar one.
  *   - Device words the library binds to a stream (the ring's relay word, the
  *     batch queue's counters) are looked up by the stream's handle.  Let a
  *     stream's work finish before destroying it if a stream created later

@@ -19,27 +19,16 @@ namespace {
 constexpr int kU = 2;
 constexpr int kB = 256;
 
+// Any element alignment of in, acc and dst (see step_tile).
 template <class T, class Op, unsigned FLAGS>
 hipError_t go(const char *in, char *acc, char *dst, size_t count, hipStream_t s)
 {
-    // acc is touched unless INIT|FINAL; dst only with FINAL.
-    constexpr bool kUsesAcc = FLAGS != (XRED_STEP_INIT | XRED_STEP_FINAL);
-    constexpr bool kUsesDst = (FLAGS & XRED_STEP_FINAL) != 0;
-    uintptr_t bits = (uintptr_t)in;
-    if (kUsesAcc) bits |= (uintptr_t)acc;
-    if (kUsesDst) bits |= (uintptr_t)dst;
-    const bool vec = (bits & 15u) == 0;
-    if (vec) {
-        const size_t nvec = count / T::kVec;
-        const size_t tail = count % T::kVec;
-        constexpr size_t kTile = (size_t)kB * kU;
-        const uint64_t tiles = (nvec + kTile - 1) / kTile + (tail ? 1 : 0);
-        return launch_kernel(step_kernel<T, Op, FLAGS, kU, kB, true>, dim3(grid_for(tiles)),
-                             dim3(kB), 0, s, in, acc, dst, nvec, tail);
-    }
-    return launch_kernel(step_kernel<T, Op, FLAGS, kU, kB, false>,
-                         dim3(grid_for((count + kB - 1) / kB)), dim3(kB), 0, s, in, acc, dst,
-                         (size_t)0, count);
+    const size_t nv = count / acc_per_vec<T>();
+    const uint32_t tail = (uint32_t)(count % acc_per_vec<T>());
+    constexpr size_t kTile = (size_t)kB * kU;
+    const uint64_t tiles = (nv + kTile - 1) / kTile + (tail ? 1 : 0);
+    return launch_kernel(step_kernel<T, Op, FLAGS, kU, kB>, dim3(grid_for(tiles)), dim3(kB), 0, s,
+                         in, acc, dst, nv, tail);
 }
 
 template <class T, class Op>
@@ -57,16 +46,12 @@ hipError_t go_flags(unsigned flags, const char *in, char *acc, char *dst, size_t
 template <class T>
 hipError_t go_cast(const char *acc, char *dst, size_t count, hipStream_t s)
 {
-    if ((((uintptr_t)acc | (uintptr_t)dst) & 15u) == 0) {
-        const size_t nvec = count / T::kVec;
-        const size_t tail = count % T::kVec;
-        constexpr size_t kTile = (size_t)kB * kU;
-        const uint64_t tiles = (nvec + kTile - 1) / kTile + (tail ? 1 : 0);
-        return launch_kernel(acc_cast_kernel<T, kU, kB, true>, dim3(grid_for(tiles)), dim3(kB),
-                             0, s, acc, dst, nvec, tail);
-    }
-    return launch_kernel(acc_cast_kernel<T, kU, kB, false>, dim3(grid_for((count + kB - 1) / kB)),
-                         dim3(kB), 0, s, acc, dst, (size_t)0, count);
+    const size_t nv = count / acc_per_vec<T>();
+    const uint32_t tail = (uint32_t)(count % acc_per_vec<T>());
+    constexpr size_t kTile = (size_t)kB * kU;
+    const uint64_t tiles = (nv + kTile - 1) / kTile + (tail ? 1 : 0);
+    return launch_kernel(acc_cast_kernel<T, kU, kB>, dim3(grid_for(tiles)), dim3(kB), 0, s, acc,
+                         dst, nv, tail);
 }
 
 }  // namespace
