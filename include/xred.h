@@ -66,11 +66,9 @@
  *     before the next 16-byte boundary are folded one by one.
  *     The same calls and items read in vectors too when only the sources
  *     share an offset and dst sits at another (a reduce-scatter shard of odd
- *     length): results are realigned across lanes and stored as aligned
- *     16-byte vectors.  They read in vectors even when their sources sit at
- *     different offsets: each source's vectors are realigned to dst's grid
- *     across lanes (calls and items shorter than a few vectors take a slower
- *     scalar path with the same results).
+ *     length), and when their sources sit at different offsets (calls and
+ *     items shorter than a vector or two take a slower scalar path with the
+ *     same results).
  *     xred_ring_reduce refuses chunks at different offsets (see there);
  *     xred_reduce_copy_step and xred_acc_cast run at one speed whatever the
  *     buffers' alignment; xred_allreduce_sim takes the vector path only when

@@ -39,6 +39,12 @@ constexpr int kStoreOut = 16;    // sc1: device scope
 constexpr int kStoreKeep = 0;    // ordinary write-back
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Global accesses at any byte alignment (the hardware realigns them).
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
+typedef u32x2 __attribute__((aligned(1))) u32x2_any;
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+typedef const __attribute__((address_space(1))) char *global_bytes;
 
 __device__ __forceinline__ rsrc_t make_rsrc(const char *base, uint32_t nbytes)
 {
@@ -55,6 +61,19 @@ template <int POL>
 __device__ __forceinline__ void bstore(u32x4 v, rsrc_t r, uint32_t off)
 {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, POL);
+}
+
+// One result vector, `o` bytes into a tile at `base` of which nrec bytes (whole
+// vectors) exist.  Off the 16-byte grid the vector is one unaligned
+// nontemporal store: the output is one stream of P + 1, and its misalignment
+// costs nothing that shows (P=8 bf16, output off the sources' grid, 4 / 16 / 128
+// MiB per source: 7.0 / 25.0 / 186 us against 6.8 / 25.1 / 192 us on it;
+// realigning the results across lanes, with narrow stores at each wavefront's
+// ends, took 7.4 / 25.7 / 195).
+__device__ __forceinline__ void store_out(u32x4 v, char *base, uint32_t nrec, uint32_t o)
+{
+    if (((uintptr_t)base & 15u) == 0) bstore<kStoreOut>(v, make_rsrc(base, nrec), o);
+    else if (o < nrec) __builtin_nontemporal_store(v, (u32x4_any *)(base + o));
 }
 
 // Bytes of a tile that exist: min(tile, total - off).
@@ -152,10 +171,64 @@ __device__ __forceinline__ void fold_groups_pipelined(typename T::Acc (&acc)[U][
     }
 }
 
+// This thread's vectors of 8 consecutive sources.
+struct Group8 {
+    u32x4 v[8];
+};
+
+// Fold sources [p0, min(nsrc, p0 + 8)) into acc, in order; source 0 starts it.
+template <class T, class Op>
+__device__ __forceinline__ void fold8(typename T::Acc (&acc)[T::kVec], const Group8 &g, int nsrc,
+                                      int p0)
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (p0 + j < nsrc) {
+            if (j == 0 && p0 == 0) up_vec<T>(g.v[0], acc);
+            else fold_vec<T, Op>(acc, g.v[j]);
+        }
+    }
+}
+
+// Issue the loads of sources [p0, p0 + 8) of one tile.  Sources past nsrc get
+// an empty range, so the number of loads in flight is known at compile time.
+template <class Src>
+__device__ __forceinline__ void fetch8(Group8 &g, const Src &src, int nsrc, int p0, Tile tl)
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const bool on = p0 + j < nsrc;
+        g.v[j] = bload<kLoadStream>(make_rsrc(src(on ? p0 + j : 0) + tl.off, on ? tl.nrec : 0u),
+                                    (uint32_t)threadIdx.x * 16u);
+    }
+}
+
+// Any number of sources, one vector per thread: groups of 8, the next group's
+// loads in flight while one is folded (fold order 0..nsrc-1).
+template <class T, class Op, class Src>
+__device__ __forceinline__ void fold_groups(typename T::Acc (&acc)[T::kVec], const Src &src,
+                                            int nsrc, Tile tl)
+{
+    Group8 a, b;
+    fetch8(a, src, nsrc, 0, tl);
+    if (nsrc <= 8) {
+        fold8<T, Op>(acc, a, nsrc, 0);
+        return;
+    }
+    for (int p0 = 0;; p0 += 16) {
+        fetch8(b, src, nsrc, p0 + 8, tl);
+        fold8<T, Op>(acc, a, nsrc, p0);
+        if (p0 + 8 >= nsrc) return;
+        fetch8(a, src, nsrc, p0 + 16, tl);
+        fold8<T, Op>(acc, b, nsrc, p0 + 8);
+        if (p0 + 16 >= nsrc) return;
+    }
+}
+
 // One tile: U vectors per thread at tile-relative vector u*B + threadIdx.x.
 // 0 < NP <= 8: exactly NP sources, all loads issued before folding;
 // NP = 16, 32, 64: whole groups of 8, software pipelined;
-// NP == 0: any nsrc > 8, folded in groups of 8 plus a remainder group.
+// NP == 0: any nsrc, in software-pipelined groups of 8 (fold_groups).
 // Every variant folds in source order 0..P-1.
 template <class T, class Op, int NP, int U, int B, class Src>
 __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst, Tile tl)
@@ -167,19 +240,8 @@ __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst,
     } else if constexpr (NP > 0) {
         fold_group<T, Op, NP, U, B, true>(acc, src, 0, tl);
     } else {
-        fold_group<T, Op, 8, U, B, true>(acc, src, 0, tl);
-        int p = 8;
-        for (; p + 8 <= nsrc; p += 8) fold_group<T, Op, 8, U, B, false>(acc, src, p, tl);
-        switch (nsrc - p) {
-        case 1: fold_group<T, Op, 1, U, B, false>(acc, src, p, tl); break;
-        case 2: fold_group<T, Op, 2, U, B, false>(acc, src, p, tl); break;
-        case 3: fold_group<T, Op, 3, U, B, false>(acc, src, p, tl); break;
-        case 4: fold_group<T, Op, 4, U, B, false>(acc, src, p, tl); break;
-        case 5: fold_group<T, Op, 5, U, B, false>(acc, src, p, tl); break;
-        case 6: fold_group<T, Op, 6, U, B, false>(acc, src, p, tl); break;
-        case 7: fold_group<T, Op, 7, U, B, false>(acc, src, p, tl); break;
-        default: break;
-        }
+        static_assert(U == 1, "runtime source counts take one vector per thread");
+        fold_groups<T, Op>(acc[0], src, nsrc, tl);
     }
     if constexpr (__is_same(Op, OpAvg)) {
         const int n = NP > 0 ? NP : nsrc;
@@ -188,10 +250,10 @@ __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst,
 #pragma unroll
             for (int j = 0; j < T::kVec; ++j) acc[u][j] = avg_scale<T, Op>(acc[u][j], n);
     }
-    const rsrc_t w = make_rsrc(dst + tl.off, tl.nrec);
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        bstore<kStoreOut>(down_vec<T, Op>(acc[u]), w, (uint32_t)(u * B + threadIdx.x) * 16u);
+        store_out(down_vec<T, Op>(acc[u]), dst + tl.off, tl.nrec,
+                  (uint32_t)(u * B + threadIdx.x) * 16u);
 }
 
 // Element i (scalar path): used for leads and tails shorter than a vector
@@ -223,8 +285,6 @@ __device__ __forceinline__ void reduce_ends(const Src &src, int nsrc, char *dst,
     const uint32_t t = threadIdx.x;
     if (t < nl + nt) reduce_elem<T, Op>(src, nsrc, dst, t < nl ? (size_t)t : tail_at + (t - nl));
 }
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Any number of sources at one 16-byte-aligned tile: the first group takes
 // up to 8 sources, then groups of 8 and a remainder, all loads of a group in
@@ -337,6 +397,85 @@ __device__ __forceinline__ void split_store(u32x4 mine, char *base, uint32_t nre
     }
 }
 
+// Sources at different offsets within 16 bytes: each vector is one unaligned
+// global load of exactly its bytes.  On whole dwords that costs no more than an
+// aligned load, off them about a fifth more (P=8 bf16, 19 MiB / 128 MiB per
+// source: aligned 28.2 / 185 us; offsets of which half are whole dwords 28.3 /
+// 186, every source 6 bytes off 34 / 222; reading aligned vectors and joining
+// neighbours' across lanes took 32.3 / 218.7 at any offsets, and the dword
+// below each vector with a lane shift of one dword 30 / 200).
+template <int G, class Src>
+__device__ __forceinline__ void fetch_any(u32x4 (&v)[G], const Src &src, int p0, size_t at,
+                                          uint32_t o)
+{
+    // both opaque, so that each load takes a scalar base and a 32-bit lane
+    // offset (64-bit lane addresses took 186 VGPRs, too many for 12 waves per CU)
+    __asm__("" : "+v"(o));
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        global_bytes base = (global_bytes)(src(p0 + j) + at);
+        __asm__("" : "+s"(base));
+        v[j] = __builtin_nontemporal_load(
+            (const __attribute__((address_space(1))) u32x4_any *)(base + o));
+    }
+}
+
+template <class T, class Op, int G, bool FIRST, class Src>
+__device__ __forceinline__ void fold_rest(typename T::Acc (&acc)[T::kVec], const Src &src, int p0,
+                                          size_t at, uint32_t o)
+{
+    u32x4 v[G];
+    fetch_any(v, src, p0, at, o);
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        if (FIRST && j == 0) up_vec<T>(v[0], acc);
+        else fold_vec<T, Op>(acc, v[j]);
+    }
+}
+
+// The last n < 8 sources, from p0 on.
+template <class T, class Op, bool FIRST, class Src>
+__device__ __forceinline__ void fold_last(typename T::Acc (&acc)[T::kVec], const Src &src, int p0,
+                                          int n, size_t at, uint32_t o)
+{
+    switch (n) {
+    case 1: fold_rest<T, Op, 1, FIRST>(acc, src, p0, at, o); break;
+    case 2: fold_rest<T, Op, 2, FIRST>(acc, src, p0, at, o); break;
+    case 3: fold_rest<T, Op, 3, FIRST>(acc, src, p0, at, o); break;
+    case 4: fold_rest<T, Op, 4, FIRST>(acc, src, p0, at, o); break;
+    case 5: fold_rest<T, Op, 5, FIRST>(acc, src, p0, at, o); break;
+    case 6: fold_rest<T, Op, 6, FIRST>(acc, src, p0, at, o); break;
+    case 7: fold_rest<T, Op, 7, FIRST>(acc, src, p0, at, o); break;
+    default: break;
+    }
+}
+
+// One tile of output vectors, one per thread: byte lb + off of dst is on a
+// 16-byte boundary, nrec > 0 bytes of the tile exist, the sources lie anywhere.
+// Groups of 8 sources, all loads of a group in flight.
+template <class T, class Op, class Src>
+__device__ __forceinline__ void offset_tile(const Src &src, int nsrc, char *dst, size_t lb,
+                                            size_t off, uint32_t nrec)
+{
+    typename T::Acc acc[T::kVec];
+    const size_t at = lb + off;
+    // lanes past the tile's end read its first vector; their store is dropped
+    const uint32_t o = threadIdx.x * 16u < nrec ? threadIdx.x * 16u : 0u;
+    if (nsrc < 8) {
+        fold_last<T, Op, true>(acc, src, 0, nsrc, at, o);
+    } else {
+        fold_rest<T, Op, 8, true>(acc, src, 0, at, o);
+        int p = 8;
+        for (; p + 8 <= nsrc; p += 8) fold_rest<T, Op, 8, false>(acc, src, p, at, o);
+        fold_last<T, Op, false>(acc, src, p, nsrc - p, at, o);
+    }
+    if constexpr (__is_same(Op, OpAvg)) {
+#pragma unroll
+        for (int e = 0; e < T::kVec; ++e) acc[e] = avg_scale<T, Op>(acc[e], nsrc);
+    }
+    bstore<kStoreOut>(down_vec<T, Op>(acc), make_rsrc(dst + at, nrec), threadIdx.x * 16u);
+}
+
 // One tile of B output vectors when the sources sit at different offsets
 // within 16 bytes: the output grid is dst's, output vector q of the tile
 // starts at byte lb + off + 16q of dst, which is 16-byte aligned, and of
@@ -405,6 +544,29 @@ __host__ __device__ __forceinline__ uint32_t shift_lead(uintptr_t dst, size_t by
     return bytes >= (size_t)lb + 32 ? lb / (uint32_t)T::kSize : 0u;
 }
 
+// How a reduction's elements are cut: `lead` of them one by one, nvec vectors,
+// the rest one by one.  Sources at one offset within 16 bytes (grid): their
+// lead ends on their next 16-byte boundary, wherever the output then lies.
+// Otherwise the output's grid rules (offset_tile).  !any: not one whole
+// vector then, or an output off its element size.
+struct VecPlan {
+    uint64_t nvec;
+    uint32_t lead;
+    bool any, grid;
+};
+
+// s0: the first source; sdiff: bits in which some source differs from it.
+template <class T>
+__host__ __device__ __forceinline__ VecPlan vec_plan(uintptr_t s0, uintptr_t sdiff, uintptr_t dst,
+                                                     uint64_t count)
+{
+    const bool grid = (sdiff & 15u) == 0 && (s0 & 15u) % T::kSize == 0;
+    const uint64_t to = ((0 - (grid ? s0 : dst)) & 15u) / T::kSize;
+    const uint32_t lead = (uint32_t)(to < count ? to : count);
+    const uint64_t nvec = (count - lead) / T::kVec;
+    return VecPlan{nvec, lead, grid || (nvec != 0 && dst % T::kSize == 0), grid};
+}
+
 // A tile whose sources sit on 16-byte boundaries (tl.off past each source
 // pointer) and whose output dst + tl.off sits c bytes past one: U vectors
 // per thread folded as reduce_tile does, then each block of B vectors
@@ -429,31 +591,43 @@ __device__ __forceinline__ void split_tile(const Src &src, int nsrc, char *dst, 
     }
 }
 
+// Work item i's tile when runs of kXcdRun consecutive tiles go to one XCD
+// (workgroup i runs on XCD i mod 8): within each block of 8 runs, XCD x takes
+// run x.  The last, partial block keeps its order.
+constexpr size_t kXcdRun = 32;
+__device__ __forceinline__ size_t xcd_run_tile(size_t i, size_t ntiles)
+{
+    if (i >= ntiles / (8 * kXcdRun) * (8 * kXcdRun)) return i;
+    return (i & ~(8 * kXcdRun - 1)) + (i & 7) * kXcdRun + ((i >> 3) & (kXcdRun - 1));
+}
+
 // ------------------------------------------------------ fused P-source --
 // dst[i] = fold_p src_p[i] for lead + nvec*kVec + tail elements, every
 // pointer at the same offset within 16 bytes: the first `lead` elements
 // (fewer than a vector) bring them all to a 16-byte boundary and, like the
 // last `tail` ones, are done by one workgroup, scalar; the nvec vectors
-// between go in tiles of B*U vectors (the last one ragged, cut by the buffer
+// between go in tiles of B vectors (the last one ragged, cut by the buffer
 // range check).  `head` (a multiple of 16 below 128, at most nvec*16) is the
 // byte length of a first, short tile that ends where the first source
 // reaches a 128-byte line: the other tiles then start on line boundaries, so
 // no line is split between two tiles (whose workgroups, on different XCDs,
 // would each fetch it).
-template <class T, class Op, int NP, int MAXP, int U, int B>
+// runs: tiles in runs of 32 per XCD (xcd_run_tile), else in address order.
+template <class T, class Op, int NP, int MAXP, int B>
 __global__ __launch_bounds__(B) void reduce_vec_kernel(KernargSrc<MAXP> src, int nsrc, char *dst,
                                                        size_t nvec, uint32_t tail, uint32_t head,
-                                                       uint32_t lead)
+                                                       uint32_t lead, bool runs)
 {
-    constexpr uint32_t kTileBytes = (uint32_t)B * U * 16u;
+    constexpr uint32_t kTileBytes = (uint32_t)B * 16u;
     const size_t vbytes = nvec * 16;
     const size_t lb = (size_t)lead * T::kSize;   // bytes before the first vector
     const uint32_t first = head != 0 ? 1u : 0u;
     const size_t ntiles = first + (vbytes - head + kTileBytes - 1) / kTileBytes;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    for (size_t i = blockIdx.x; i < ntiles; i += gridDim.x) {
+        const size_t t = runs ? xcd_run_tile(i, ntiles) : i;
         const bool h = t < first;
         const size_t off = h ? 0 : head + (t - first) * kTileBytes;
-        reduce_tile<T, Op, NP, U, B>(src, nsrc, dst,
+        reduce_tile<T, Op, NP, 1, B>(src, nsrc, dst,
                                      Tile{lb + off, h ? head : tile_nrec(vbytes, off, kTileBytes)});
     }
     if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)
@@ -482,10 +656,6 @@ __global__ __launch_bounds__(B) void reduce_scalar_kernel(KernargSrc<XRED_MAX_SR
 // the hardware realigns (chunks cut at odd lengths: bf16 4M elements 11 us
 // element by element, 6.3 now); the accumulator's buffer accesses need only
 // 4-byte alignment, which every accumulator has.
-typedef u32x4 __attribute__((aligned(1))) u32x4_any;
-typedef u32x2 __attribute__((aligned(1))) u32x2_any;
-typedef uint32_t __attribute__((aligned(1))) u32_any;
-
 // Input or output bytes of one accumulator vector.
 template <class T>
 constexpr int part_bytes() { return acc_per_vec<T>() * T::kSize; }

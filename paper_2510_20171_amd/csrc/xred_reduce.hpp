@@ -15,21 +15,16 @@
 namespace xred {
 namespace {
 
-// Three tile shapes:
+// Two tile shapes, one 16-byte vector of every source per thread:
 //
-// * Launches that fit on the chip in one round (every tile resident at
-//   once) are latency-bound: they use 512-thread workgroups of one 16-byte
-//   vector per thread, uncapped, so the whole message is in flight after the
-//   fewest workgroup dispatches (8 MiB per source at P=8 bf16: 10.1 us
-//   against 10.8 us with 128-thread workgroups, same process and buffers).
-// * Up to 8 sources, launches that fit in one round with two vectors per
-//   thread (bf16: 8-16 MiB per source) use that shape too, still uncapped:
-//   one round of dispatches instead of several rounds of 128-thread
-//   workgroups (P=8 bf16, back to back / cold: 12 MiB 15.6 / 21.1 us against
-//   17.4 / 22.4; 16 MiB 21.9 / 27.2 against 25.1 / 30.2; P=4 fp32 16 MiB
-//   11.1 against 12.1 us; from 20 MiB on the 128-thread shape is as fast).
-//   Three, four, six or eight vectors per thread at 20-64 MiB gained at most
-//   a few percent and lost 6 % on P=8 fp32 at 32 MiB, so they are not used.
+// * Up to 8 sources, launches that fit on the chip in one round (every tile
+//   resident at once: up to 8 MiB per source) are latency-bound: 512-thread
+//   workgroups, uncapped, so the whole message is in flight after the fewest
+//   workgroup dispatches (P=8 bf16 4 MiB per source 6.8 us against 7.0-7.4
+//   with 128 threads; equal at 7 MiB).  More sources are bound by what a
+//   CU keeps in flight, so they spread over the chip in 128-thread
+//   workgroups at any size (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us
+//   against 8.1 / 23.6 / 41.6).
 // * Larger launches are bandwidth-bound: 128-thread workgroups with a
 //   bounded number of waves per CU.  HBM3E on MI355X delivers the most when
 //   a CU keeps a moderate number of loads in flight; more waves than that
@@ -41,17 +36,38 @@ namespace {
 //   workgroup an LDS reservation it never touches, sized so that only the
 //   wanted number of workgroups fit on a CU.
 // * Five to eight sources want more loads in flight when each holds several
-//   hundred MiB, and when a launch is only a few rounds long (P=8 bf16, one
-//   process per setting, best cap and time against the 12-wave cap: 16 MiB
-//   per source 24, 25.5 us against 27.4 us back to back and 30.0 against
-//   32.0 us cold; 32 MiB 12 (24: +4 % cold); 128 MiB 12; 256 MiB 16, 360 us
-//   against 374 us; 512 MiB 24, 830 us against 963 us; 768 MiB 20-24, 1232 us
-//   against 1346 us).  16 and 32 sources keep their caps up to 4.4 GB.
-constexpr int kU = 1;          // 16-byte vectors per thread per tile
+//   hundred MiB, and when a launch is only a few rounds long (P=8 bf16: 9 / 11 /
+//   13 / 16 / 24 MiB in runs at 12 waves 14.3 / 17.1 / 19.6 / 23.5 / 34.1 us, at
+//   16 waves 14.0 / 16.7 / 19.5 / 23.4 / 34.5; 32 MiB and 128 MiB 12; 256 MiB
+//   16, 360 us against 374 us; 512 MiB 24, 830 us against 963 us; 768 MiB 20-24,
+//   1232 us against 1346 us).  16 and 32 sources keep their caps up to 4.4 GB.
+//
+// Tile order of the 128-thread shape.  In address order, with one 2 KiB tile
+// per workgroup, XCD x reads the 2 KiB blocks x mod 8 of every stream.  That is
+// as good as any order only while all streams' blocks coincide: the buffers'
+// bases on 2 KiB boundaries and equal modulo 16 KiB.  Runs of 32 tiles per XCD
+// (64 KiB) do not depend on it, and let an XCD's L2 serve the lines that tiles
+// off line boundaries share (P=8 bf16, bases at multiples of 512 B / 128 B /
+// odd multiples of 4 KiB: 64 MiB 91.3 / 95.1 / 107.6 -> 89.2 / 89.4 / 90.3 us,
+// 128 MiB 189.9 / 195.0 / 217.5 -> 191.4 / 190.4 / 194.6; 16 MiB 25.2 -> 24.1 and, on
+// equal bases, 25.2 us with two vectors per 512-thread workgroup -> 23.5).
+// With equal bases address order wins from about 512 MiB of sources up (P=8
+// 64 MiB 87.4 against 86.9 in runs, 128 MiB 179.9 / 183.7; P=4 64 MiB 49.3 /
+// 48.8, 128 MiB 104.7 / 106.2; P=32 16 MiB 86.6 / 86.8, 32 MiB 169.3 / 173.4).
 constexpr int kB = 128;        // threads per workgroup, bandwidth-bound launches
 constexpr int kBWide = 512;    // threads per workgroup, one-round launches
 constexpr int kWideWgsPerCu = 4;   // resident 512-thread workgroups per CU
-constexpr int kUWide2 = 2;         // vectors per thread of the second one-round shape (NP <= 8)
+
+bool run_order(const char *const *srcs, int nsrc, const char *dst, size_t bytes)
+{
+    if ((size_t)nsrc * bytes <= ((size_t)512 << 20)) return true;
+    uintptr_t any = (uintptr_t)dst, diff = 0;
+    for (int p = 0; p < nsrc; ++p) {
+        any |= (uintptr_t)srcs[p];
+        diff |= (uintptr_t)srcs[p] ^ (uintptr_t)dst;
+    }
+    return (any & 2047u) != 0 || (diff & 16383u) != 0;
+}
 
 // Waves per CU for a compile-time source count (NP = 0, a runtime count: see
 // waves_for); 0 = no cap.
@@ -85,7 +101,7 @@ int waves_for(size_t bytes, int nsrc)
     if (NP >= 5 && NP <= 8) {
         if (bytes > ((size_t)384 << 20)) return 24;
         if (bytes > ((size_t)192 << 20)) return waves_per_cu<NP>() > 16 ? waves_per_cu<NP>() : 16;
-        if (bytes <= ((size_t)24 << 20)) return 24;
+        if (bytes <= ((size_t)24 << 20)) return waves_per_cu<NP>() > 16 ? waves_per_cu<NP>() : 16;
     }
     return waves_per_cu<NP>();
 }
@@ -104,61 +120,28 @@ size_t lds_for_waves(int waves)
     return (size_t)(lds_per_cu() / wgs) / 512 * 512;
 }
 
-// ------------------------------------------------- split destination --
-// Sources at one offset m within 16 bytes, the destination at another (a
-// reduce-scatter shard of odd length leaves every rank's shard but some in
-// this case): after `lead` elements every source is on a 16-byte boundary
-// and is read in vectors as in reduce_vec_kernel, and each tile's results are
-// realigned to dst's 16-byte grid and stored in aligned vectors (split_tile).
-// P=8 bf16, 16 MiB per source: 51 us element by element, 32 us storing every
-// result in 2-byte pieces, 24 us realigned (23.3 us with every buffer
-// aligned).  Any source count; the vector path's three shapes: launches
-// that fit on the chip in one round take 512-thread workgroups of one vector
-// per thread, or (up to 8 sources) two, the others 128-thread workgroups
-// under the vector path's occupancy cap.
-// reduce_vec_kernel's tiles (U = 1) through split_tile; tail and lead as
-// there.
-template <class T, class Op, int U, int B>
-__global__ __launch_bounds__(B) void reduce_split_kernel(KernargSrc<XRED_MAX_SRC> src, int nsrc,
-                                                         char *dst, size_t nvec, uint32_t tail,
-                                                         uint32_t head, uint32_t lead, uint32_t c)
-{
-    constexpr uint32_t kTileBytes = (uint32_t)B * U * 16u;
-    const size_t vbytes = nvec * 16;
-    const size_t lb = (size_t)lead * T::kSize;
-    const uint32_t first = head != 0 ? 1u : 0u;
-    const size_t ntiles = first + (vbytes - head + kTileBytes - 1) / kTileBytes;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const bool h = t < first;
-        const size_t off = h ? 0 : head + (t - first) * kTileBytes;
-        split_tile<T, Op, U, B>(src, nsrc, dst,
-                             Tile{lb + off, h ? head : tile_nrec(vbytes, off, kTileBytes)}, c);
-    }
-    if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)
-        reduce_ends<T, Op>(src, nsrc, dst, lead, tail, lead + nvec * T::kVec);
-}
-
-// --------------------------------------------------- shifted sources --
-// Sources at different offsets within 16 bytes: the output grid is dst's.
-// The first `lead` elements reach dst's next 16-byte boundary and one vector
-// more, so every source's aligned base lies inside it, and nvec stops a
-// vector short of every source's end; the tiles between are shift_tile's,
-// the lead and the tail are folded element by element.  (P=8 x 64M bf16
-// with the sources at alternating offsets: 574 us element by element.)
+// ------------------------------------------------- sources at offsets --
+// Sources at different offsets within 16 bytes (views into flat buffers laid
+// out differently): the output grid is dst's after `lead` elements, and every
+// source is read in vectors where it lies (offset_tile).
+//
+// Tiles go in runs per XCD whatever the size (mixed offsets, 12 waves per CU,
+// in address order against runs: 19 MiB per source 29.9 / 28.3 us, 128 MiB
+// 190.8 / 185.8 us).
 template <class T, class Op, int B>
-__global__ __launch_bounds__(B) void reduce_shift_kernel(KernargSrc<XRED_MAX_SRC> src, int nsrc,
-                                                         char *dst, size_t nvec, uint32_t tail,
-                                                         uint32_t lead)
+__global__ __launch_bounds__(B) void reduce_offset_kernel(KernargSrc<XRED_MAX_SRC> src, int nsrc,
+                                                          char *dst, size_t nvec, uint32_t tail,
+                                                          uint32_t lead)
 {
     constexpr uint32_t kTileBytes = (uint32_t)B * 16u;
     const size_t vbytes = nvec * 16;
     const size_t lb = (size_t)lead * T::kSize;
     const size_t ntiles = (vbytes + kTileBytes - 1) / kTileBytes;
     for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const size_t off = t * kTileBytes;
-        shift_tile<T, Op, B>(src, nsrc, dst, lb, off, tile_nrec(vbytes, off, kTileBytes));
+        const size_t off = xcd_run_tile(t, ntiles) * kTileBytes;
+        offset_tile<T, Op>(src, nsrc, dst, lb, off, tile_nrec(vbytes, off, kTileBytes));
     }
-    if (blockIdx.x == ntiles % gridDim.x)
+    if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)
         reduce_ends<T, Op>(src, nsrc, dst, lead, tail, lead + nvec * T::kVec);
 }
 
@@ -183,34 +166,21 @@ int waves_split(size_t bytes, int nsrc)
 }
 
 template <class T, class Op>
-hipError_t go_split(const char *const *srcs, int nsrc, char *dst, size_t count, uint32_t lead,
-                    hipStream_t s)
+hipError_t go_offset(const char *const *srcs, int nsrc, char *dst, size_t count, const VecPlan &vp,
+                     hipStream_t s)
 {
     KernargSrc<XRED_MAX_SRC> ks;
     for (int p = 0; p < nsrc; ++p) ks.p[p] = srcs[p];
     for (int p = nsrc; p < XRED_MAX_SRC; ++p) ks.p[p] = nullptr;
-    const size_t nvec = (count - lead) / T::kVec;
-    const uint32_t tail = (uint32_t)((count - lead) % T::kVec);
-    const size_t mis = ((uintptr_t)srcs[0] + (size_t)lead * T::kSize) & 127u;
-    const uint32_t head = (uint32_t)(mis == 0 ? 0 : std::min<size_t>(128 - mis, nvec * 16));
-    const size_t hv = head / 16, first = head != 0 ? 1 : 0;
-    const uint32_t c = (uint32_t)(((uintptr_t)dst + (size_t)lead * T::kSize) & 15u);
-    const uint64_t extra = (tail | lead) ? 1 : 0;
-    const uint64_t one_round = (uint64_t)device_cus() * kWideWgsPerCu;
-    const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
-    if (tiles_wide <= one_round)
-        return launch_kernel(reduce_split_kernel<T, Op, 1, kBWide>, dim3(grid_for(tiles_wide)),
-                             dim3(kBWide), 0, s, ks, nsrc, dst, nvec, tail, head, lead, c);
-    constexpr size_t kTileWide2 = (size_t)kBWide * kUWide2;
-    const uint64_t tiles_wide2 = first + (nvec - hv + kTileWide2 - 1) / kTileWide2 + extra;
-    if (nsrc <= 8 && tiles_wide2 <= one_round)
-        return launch_kernel(reduce_split_kernel<T, Op, kUWide2, kBWide>,
-                             dim3(grid_for(tiles_wide2)), dim3(kBWide), 0, s, ks, nsrc, dst, nvec,
-                             tail, head, lead, c);
-    const uint64_t tiles = first + (nvec - hv + kB - 1) / kB + extra;
-    return launch_kernel(reduce_split_kernel<T, Op, 1, kB>, dim3(grid_for(tiles)), dim3(kB),
-                         lds_for_waves(waves_split<T>(count * T::kSize, nsrc)), s, ks, nsrc, dst,
-                         nvec, tail, head, lead, c);
+    const size_t bytes = count * T::kSize, nvec = vp.nvec;
+    const uint32_t tail = (uint32_t)(count - vp.lead - nvec * T::kVec);
+    const dim3 grid(grid_for((nvec + kB - 1) / kB + ((tail | vp.lead) ? 1 : 0)));
+    // 12 waves also for 5-8 sources of at most 24 MiB, unlike the vector path
+    // (mixed offsets at 19 MiB, 12 / 16 / 24 waves: 28.3 / 29.0 / 30.6 us)
+    const int waves = nsrc >= 5 && nsrc <= 8 && bytes <= ((size_t)192 << 20)
+                          ? 12 : waves_split<T>(bytes, nsrc);
+    return launch_kernel(reduce_offset_kernel<T, Op, kB>, grid, dim3(kB), lds_for_waves(waves), s,
+                         ks, nsrc, dst, nvec, tail, vp.lead);
 }
 
 template <class T, class Op, int NP, int MAXP>
@@ -226,64 +196,32 @@ hipError_t go_vec(const char *const *srcs, int nsrc, char *dst, size_t count, ui
     const size_t mis = ((uintptr_t)srcs[0] + (size_t)lead * T::kSize) & 127u;
     const uint32_t head = (uint32_t)(mis == 0 ? 0 : std::min<size_t>(128 - mis, nvec * 16));
     const size_t hv = head / 16, first = head != 0 ? 1 : 0;
-    constexpr size_t kTileWide = (size_t)kBWide * kU;
-    const uint64_t tiles_wide = first + (nvec - hv + kTileWide - 1) / kTileWide + ((tail | lead) ? 1 : 0);
-    const uint64_t one_round = (uint64_t)device_cus() * kWideWgsPerCu;
-    if (tiles_wide <= one_round)
-        return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kU, kBWide>,
-                             dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst, nvec,
-                             tail, head, lead);
+    const uint64_t extra = (tail | lead) ? 1 : 0;
     if constexpr (NP >= 1 && NP <= 8) {
-        constexpr size_t kTileWide2 = (size_t)kBWide * kUWide2;
-        const uint64_t tiles_wide2 =
-            first + (nvec - hv + kTileWide2 - 1) / kTileWide2 + ((tail | lead) ? 1 : 0);
-        if (tiles_wide2 <= one_round)
-            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kUWide2, kBWide>,
-                                 dim3(grid_for(tiles_wide2)), dim3(kBWide), 0, s, ks, nsrc, dst,
-                                 nvec, tail, head, lead);
+        const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
+        if (tiles_wide <= (uint64_t)device_cus() * kWideWgsPerCu)
+            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kBWide>,
+                                 dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst,
+                                 nvec, tail, head, lead, false);
     }
-    constexpr size_t kTile = (size_t)kB * kU;
-    const uint64_t tiles = first + (nvec - hv + kTile - 1) / kTile + ((tail | lead) ? 1 : 0);
-    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kU, kB>, dim3(grid_for(tiles)),
-                         dim3(kB), lds_for_waves(waves_for<T, NP>(count * T::kSize, nsrc)), s, ks, nsrc,
-                         dst, nvec, tail, head, lead);
+    const uint64_t tiles = first + (nvec - hv + kB - 1) / kB + extra;
+    const size_t bytes = count * T::kSize;
+    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kB>, dim3(grid_for(tiles)), dim3(kB),
+                         lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst, nvec,
+                         tail, head, lead, run_order(srcs, nsrc, dst, bytes));
 }
 
 template <class T, class Op>
 hipError_t go(const char *const *srcs, int nsrc, char *dst, size_t count, hipStream_t s)
 {
-    // Pointers all at one offset m within 16 bytes (views at one element
-    // offset, a reduce-scatter shard) take the vector path after `lead`
-    // elements that bring them to a 16-byte boundary; sources at different
-    // offsets read realigned vectors (reduce_shift_kernel) unless the call
-    // is too short, which is scalar.
-    // Sources at one offset and dst at another take the vector loads with
-    // split stores.
-    const uintptr_t m = (uintptr_t)srcs[0] & 15u;
-    bool common = true;
-    for (int p = 1; p < nsrc; ++p) common = common && ((uintptr_t)srcs[p] & 15u) == m;
-    const uint32_t lead = m == 0 ? 0u : (uint32_t)((16 - m) / T::kSize);
-    if (common && lead < count && ((uintptr_t)dst & 15u) != m)
-        return go_split<T, Op>(srcs, nsrc, dst, count, lead, s);
-    if (!common) {
-        // dst's next 16-byte boundary and one vector more, then vectors up to
-        // a vector short of the end (see reduce_shift_kernel)
-        const size_t bytes = count * T::kSize;
-        const uint32_t slead = shift_lead<T>((uintptr_t)dst, bytes);
-        const size_t slb = (size_t)slead * T::kSize;
-        if (slead != 0) {
-            KernargSrc<XRED_MAX_SRC> ks;
-            for (int p = 0; p < nsrc; ++p) ks.p[p] = srcs[p];
-            for (int p = nsrc; p < XRED_MAX_SRC; ++p) ks.p[p] = nullptr;
-            const size_t nvec = (bytes - slb - 16) / 16;
-            const uint32_t tail = (uint32_t)(count - slead - nvec * T::kVec);
-            const uint64_t tiles = (nvec + kB - 1) / kB + 1;
-            return launch_kernel(reduce_shift_kernel<T, Op, kB>, dim3(grid_for(tiles)), dim3(kB),
-                                 lds_for_waves(waves_split<T>(bytes, nsrc)), s, ks, nsrc, dst,
-                                 nvec, tail, slead);
-        }
-    }
-    if (!common || lead >= count) {
+    // Sources at one offset within 16 bytes (views at one element offset, a
+    // reduce-scatter shard) take the vector path, whatever dst's; others read
+    // vectors where they lie (go_offset) unless the call is too short, which
+    // is scalar.
+    uintptr_t sdiff = 0;
+    for (int p = 1; p < nsrc; ++p) sdiff |= (uintptr_t)srcs[p] ^ (uintptr_t)srcs[0];
+    const VecPlan vp = vec_plan<T>((uintptr_t)srcs[0], sdiff, (uintptr_t)dst, count);
+    if (!vp.any) {
         KernargSrc<XRED_MAX_SRC> ks;
         for (int p = 0; p < nsrc; ++p) ks.p[p] = srcs[p];
         for (int p = nsrc; p < XRED_MAX_SRC; ++p) ks.p[p] = nullptr;
@@ -291,6 +229,8 @@ hipError_t go(const char *const *srcs, int nsrc, char *dst, size_t count, hipStr
                              dim3(grid_for((count + kB - 1) / kB)), dim3(kB), 0, s, ks, nsrc, dst,
                              count);
     }
+    if (!vp.grid) return go_offset<T, Op>(srcs, nsrc, dst, count, vp, s);
+    const uint32_t lead = vp.lead;
     constexpr bool kWide = is_core_type<T>() && !__is_same(Op, OpAvg);
     switch (nsrc) {
     case 1: return go_vec<T, Op, 1, 8>(srcs, nsrc, dst, count, lead, s);

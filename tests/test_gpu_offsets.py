@@ -1,0 +1,77 @@
+"""Fused reduces whose sources and output sit at different offsets within 16
+bytes: vectors read where they lie (whole dwords, or off the dword grid), one
+and several groups of 8 sources, lengths at the edges of the lead, of a
+vector, of a 128-vector tile and of the runs of 32 tiles per XCD, in place and
+out of place, with guard bands around the output.  Bit-exact against the CPU
+oracle."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+import pins
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+PAD = 64
+
+
+@pytest.fixture(scope="module")
+def xr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    import paper_2510_20171_amd as xr
+    xr.load()
+    return xr
+
+
+def _run(xr, orc, dtype, op, P, n, src_off, dst_off, seed, in_place=False):
+    rng = np.random.default_rng(seed)
+    base = [pins.random_column_values(rng, dtype, n) for _ in range(min(P, 9))]
+    srcs = [np.roll(base[p % len(base)], p // len(base)) for p in range(P)]
+    dev = []
+    for p, v in enumerate(srcs):
+        buf = np.full(src_off[p] + n + PAD, v[0], v.dtype)
+        buf[src_off[p]:src_off[p] + n] = v
+        dev.append(gu.to_dev(buf, dtype)[src_off[p]:src_off[p] + n])
+    es = np.dtype(gu.NP_BITS[dtype]).itemsize
+    what = f"{dtype} {op} P={P} n={n} src={src_off[:9]} dst={dst_off} in_place={in_place}"
+    if in_place:
+        out, raw = dev[P // 2], None
+    else:
+        raw = torch.full(((dst_off + n + PAD) * es,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = raw[dst_off * es:(dst_off + n) * es].view(gu.torch_dtype(dtype))
+    xr.allreduce_local(dev, out, op, dtype=dtype)
+    torch.cuda.synchronize()
+    gu.assert_parity(out, orc.allreduce_local(srcs, dtype, op), dtype, op, what)
+    if raw is not None:
+        r = raw.cpu().numpy()
+        assert (r[:dst_off * es] == 0xA5).all() and (r[(dst_off + n) * es:] == 0xA5).all(), what
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "e4m3", "i8", "f32", "f64"])
+@pytest.mark.parametrize("P", [1, 2, 8, 9, 16, 17, 33, 64])
+def test_offsets(xr, orc, dtype, P):
+    es = np.dtype(gu.NP_BITS[dtype]).itemsize
+    vec = 16 // es
+    op = "avg" if dtype in ("f16", "f64") and P > 1 else "sum"
+    whole = [4 * ((p * 3 + 1) % 4) // es if es < 4 else (p * 3 + 1) % vec for p in range(P)]
+    odd = [(p * 5 + 1) % vec for p in range(P)]
+    same = [1] * P                      # one offset for all sources, another for the output
+    for src_off, dst_off in ((whole, 0), (odd, 0), (odd, 3 % vec), (same, 0), (same, 2 % vec)):
+        for n in (1, 2 * vec - 1, 3 * vec, 5 * vec + 1, 128 * vec + 2, 1000 * vec + 5):
+            _run(xr, orc, dtype, op, P, n, src_off, dst_off, 100 * P + n)
+        _run(xr, orc, dtype, "max", P, 777 * vec + 3, src_off, dst_off, P, in_place=True)
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1, 129])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_offsets_xcd_runs(xr, orc, dtype, extra):
+    vec = 16 // np.dtype(gu.NP_BITS[dtype]).itemsize
+    for blocks in (1, 3):               # 256 tiles of 128 vectors are one block of runs
+        n = (blocks * 256 * 128 + extra) * vec + 3
+        _run(xr, orc, dtype, "sum", 3, n, [1, 0, 3], 0, n)
+        prev = xr.set_max_workgroups(37)
+        try:
+            _run(xr, orc, dtype, "sum", 3, n, [1, 0, 3], 2, n)
+        finally:
+            xr.set_max_workgroups(prev)
