@@ -239,7 +239,7 @@ XRED_API xred_status xred_acc_cast(const void *acc, void *dst, size_t count, xre
  *            read when the kernels run, so an earlier kernel on the stream may
  *            still write them (metadata by reference, after the GPU-resident
  *            collectives of Section 6.1).  No host work per item: the kernel
- *            plans the batch from the descriptors.  Batches of 65..16384
+ *            plans the batch from the descriptors.  Batches of up to 16384
  *            items launched eagerly take tiles in order from a counter pair
  *            in device memory the library binds to the calling stream (64
  *            streams per device, allocated once, until xred_release);

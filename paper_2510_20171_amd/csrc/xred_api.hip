@@ -590,13 +590,9 @@ int current_device_index()
 // XRED_MAX_WORKGROUPS environment variable at load); read on every launch.
 std::atomic<unsigned> g_max_workgroups{(unsigned)env_long("XRED_MAX_WORKGROUPS", 0)};
 
-// Device-descriptor batches: items per run and workgroups per CU of the
-// grouped kernel (measured on the 4096-item log-uniform batch: 32 / 64 / 96 /
-// 128 items per run 5.44-5.50 / 5.69-5.70 / 5.49-5.51 / 5.36-5.38 TB/s; 64
-// also best on equal items), and workgroups per CU of the queue kernel (one:
-// a second widens the window of tiles being read, 1265 against 1301 us).
-constexpr int kGroupedRunItems = 64;
-constexpr int kGroupedWgsPerCu = 2;
+// Device-descriptor batches: workgroups per CU of the queue kernel (one: a
+// second widens the window of tiles being read, 1265 against 1301 us on the
+// 4096-item log-uniform batch).
 constexpr int kQueueWgsPerCu = 1;
 
 unsigned grid_for(uint64_t tiles)
@@ -613,13 +609,10 @@ unsigned batched_device_grid()
     return grid_for((uint64_t)device_cus() * (uint64_t)per_cu);
 }
 
-// Device-resident descriptors, more than one run of items.  Batches of one
-// run keep the round-robin kernel: within a run the split is fixed, and the
-// round-robin kernel's larger tiles stream large items faster (64 items of
-// 8 MiB per source: 5.0 against 4.8 TB/s).  Grouped kernel: runs of
-// kGroupedRunItems consecutive items, each dealt to the workgroups that fit on
-// the chip at once; under a CU budget, fewer workgroups per run and fewer runs
-// at a time.
+// Device-resident descriptors: the queue kernel, or under graph capture (a
+// replay would repeat the captured counter), past the queue's item limit, or
+// without a slot, the stateless runs kernel.  Under a CU budget the latter
+// takes fewer workgroups per run and fewer runs at a time.
 hipError_t batched_device(const xred_item *items, int nitems, xred_dtype dtype, xred_op op,
                           hipStream_t stream)
 {
@@ -640,18 +633,15 @@ hipError_t batched_device(const xred_item *items, int nitems, xred_dtype dtype, 
             return e;
         }
     }
-    // Under graph capture (a replay would repeat the captured counter), past
-    // the queue's item limit, or without a slot: the stateless grouped kernel.
-    const uint64_t per_run =
-        (uint64_t)std::min(kGroupedRunItems, batched_grouped_max_items());   // LDS prefix size
-    const uint64_t ngroups = ((uint64_t)nitems + per_run - 1) / per_run;
+    const uint64_t per_run = (uint64_t)batched_run_items();
+    const uint64_t nruns = ((uint64_t)nitems + per_run - 1) / per_run;
     const unsigned cap = g_max_workgroups.load(std::memory_order_relaxed);
-    uint64_t m = (uint64_t)device_cus() * kGroupedWgsPerCu;
+    uint64_t m = (uint64_t)device_cus();
     if (cap != 0 && m > cap) m = cap;
     const uint64_t max_sets = (cap != 0 ? (uint64_t)cap : 0x7FFFFFFFull) / m;
-    const uint64_t sets = ngroups < max_sets ? ngroups : max_sets;
-    return launch_batched_grouped(dtype, op, items, nitems, (uint32_t)ngroups, (uint32_t)m,
-                                  (unsigned)(m * sets), kGroupedWgsPerCu, stream);
+    const uint64_t sets = nruns < max_sets ? nruns : max_sets;
+    return launch_batched_runs(dtype, op, items, nitems, (uint32_t)nruns, (uint32_t)m,
+                               (unsigned)(m * sets), stream);
 }
 
 unsigned batched_rr_grid(int fit_per_cu)
@@ -833,10 +823,7 @@ XRED_API xred_status xred_batched_reduce(const xred_item *items, int nitems, xre
     if (flags & XRED_ITEMS_ON_DEVICE) {
         if ((uintptr_t)items % alignof(xred_item))
             return fail(XRED_INVALID_ARGUMENT, "items is not %zu-byte aligned", alignof(xred_item));
-        const hipError_t e =
-            nitems <= kGroupedRunItems
-                ? launch_batched_rr(dtype, op, items, nitems, nullptr, (hipStream_t)hip_stream)
-                : batched_device(items, nitems, dtype, op, (hipStream_t)hip_stream);
+        const hipError_t e = batched_device(items, nitems, dtype, op, (hipStream_t)hip_stream);
         return e == hipSuccess ? XRED_SUCCESS : hip_fail(e, "batched launch");
     }
     return batched_host(items, nitems, dtype, op, (hipStream_t)hip_stream);

@@ -60,25 +60,20 @@ hipError_t launch_batched_table(xred_dtype dtype, xred_op op, const xred_item *d
 
 int batched_rr_max_items() { return kRrMaxItems; }
 
-int batched_grouped_max_items() { return kGrpMaxItems; }
+int batched_run_items() { return kRunItems; }
 
-hipError_t launch_batched_grouped(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                  int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                  int wgs_per_cu, hipStream_t stream)
+hipError_t launch_batched_runs(xred_dtype dtype, xred_op op, const xred_item *d_items, int nitems,
+                               uint32_t nruns, uint32_t m, unsigned grid, hipStream_t stream)
 {
     switch (group_of(dtype)) {
     case TypeGroup::kFloat:
-        return launch_batched_grouped_float(dtype, op, d_items, nitems, ngroups, m, grid,
-                                            wgs_per_cu, stream);
+        return launch_batched_runs_float(dtype, op, d_items, nitems, nruns, m, grid, stream);
     case TypeGroup::kFp8:
-        return launch_batched_grouped_fp8(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+        return launch_batched_runs_fp8(dtype, op, d_items, nitems, nruns, m, grid, stream);
     case TypeGroup::kExt:
-        return launch_batched_grouped_ext(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+        return launch_batched_runs_ext(dtype, op, d_items, nitems, nruns, m, grid, stream);
     default:
-        return launch_batched_grouped_int(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+        return launch_batched_runs_int(dtype, op, d_items, nitems, nruns, m, grid, stream);
     }
 }
 

@@ -5,23 +5,21 @@
 // Small messages are dominated by per-call overhead (the T_c term of the
 // LogP model in Section 6.2), so a batch of K reductions is run as one
 // kernel.  Work is cut into tiles of 16-byte vectors of one item, in the
-// global order item 0's tiles, then item 1's, ...  Four kernels:
+// global order item 0's tiles, then item 1's, ...  Five kernels:
 //   table        (host descriptors, the usual case): the host stages the
 //                item of every tile and one workgroup runs each tile, so the
 //                hardware dispatches tiles in order, as for the fused kernel;
-//   grouped      (device descriptors, more than one run of items): runs of
-//                consecutive items, each dealt tile by tile to its own set of
-//                workgroups, which plan their tiles from the descriptors in the
-//                kernel (metadata by reference, Section 6.1); the sets are
-//                dispatched in order, so the runs balance over the chip;
-//   round-robin  (device descriptors of one run, or host batches past the
-//                table's size): a persistent grid, tile g on workgroup g mod G,
-//                the tile-start prefix in LDS (staged, or scanned from the
-//                descriptors in the kernel);
+//   queue        (device descriptors, eager): a persistent grid takes tiles
+//                in order from a counter in device memory;
+//   runs         (device descriptors under graph capture, or past the queue's
+//                limits): runs of up to 64 consecutive items, each dealt tile
+//                by tile to its own set of workgroups, whose waves plan their
+//                tiles from the descriptors in registers (metadata by
+//                reference, Section 6.1); no state between calls;
+//   round-robin  (host batches past the table's size): a persistent grid,
+//                tile g on workgroup g mod G, the tile-start prefix staged;
 //   range        (host batches past the round-robin plan's items): contiguous
 //                tile ranges per workgroup, planned on the host.
-// Device-descriptor kernels keep no state between calls, so they can be
-// captured in a graph.
 
 #pragma once
 
@@ -52,24 +50,11 @@ __device__ __forceinline__ bool item_runnable(const xred_item &it)
            it.dst != nullptr;
 }
 
-template <class T, bool CHECK>
+// Tiles of an item (0: nothing to run, or a descriptor that cannot be run).
+template <class T>
 __device__ __forceinline__ uint64_t item_tiles(const xred_item &it)
 {
-    if (CHECK && !item_runnable(it)) return 0;
-    return (it.count + tile_elems<T>() - 1) / tile_elems<T>();
-}
-
-// Descriptor of item k, loaded field by field with scalar loads.
-__device__ __forceinline__ xred_item load_item(const xred_item *items, uint64_t k)
-{
-    const xred_item *p = items + k;
-    xred_item it;
-    it.srcs = sload(&p->srcs);
-    it.dst = sload(&p->dst);
-    it.count = sload(&p->count);
-    it.nsrc = sload(&p->nsrc);
-    it.reserved = sload(&p->reserved);
-    return it;
+    return item_runnable(it) ? (it.count + tile_elems<T>() - 1) / tile_elems<T>() : 0;
 }
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t x)
@@ -79,159 +64,206 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Inclusive prefix sum over the workgroup; s[kB-1] holds the total until the
-// next call.
-__device__ uint64_t block_inclusive_scan(uint64_t v, uint64_t *s)
+// v plus the value a DPP move brings from a lower lane (0 where none does).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_add(uint64_t v)
 {
-    __syncthreads();
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < kB; off <<= 1) {
-        const uint64_t t = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
-    }
-    return s[threadIdx.x];
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
+    return v + (((uint64_t)hi << 32) | lo);
 }
 
-// Exclusive prefix sum over the workgroup (kB threads); *total gets the sum.
-__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t *s_wave,
-                                                         uint64_t *total)
+// Inclusive prefix sum over the wavefront: within rows of 16 lanes by
+// row_shr:1, 2, 4, 8, then row_bcast:15 into rows 1 and 3 and row_bcast:31
+// into rows 2 and 3.  All in the vector ALU (64-bit shuffles through LDS
+// took 0.4 us a scan, on the critical path of every small batch).
+__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v)
+{
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    return dpp_add<0x143, 0xc>(v);
+}
+
+// Exclusive prefix sum of v over the workgroup (kB threads); *total gets the
+// sum, *wsum the sum of w.  s_wave: 2 * kB / 64 words of LDS.
+__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t w, uint64_t *s_wave,
+                                                         uint64_t *total, uint64_t *wsum)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint64_t t = __shfl_up(incl, (unsigned)off, 64);
-        if (lane >= off) incl += t;
+    const uint64_t incl = wave_inclusive_scan(v);
+    w = wave_inclusive_scan(w);
+    if (lane == 63) {
+        s_wave[2 * wave] = incl;
+        s_wave[2 * wave + 1] = w;
     }
-    if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    uint64_t before = 0, sum = 0;
+    uint64_t before = 0, sum = 0, ws = 0;
 #pragma unroll
-    for (int w = 0; w < kB / 64; ++w) {
-        const uint64_t x = s_wave[w];
-        before += w < wave ? x : 0;
+    for (int i = 0; i < kB / 64; ++i) {
+        const uint64_t x = s_wave[2 * i];
+        before += i < wave ? x : 0;
         sum += x;
+        ws += s_wave[2 * i + 1];
     }
     *total = sum;
+    *wsum = ws;
     return before + incl - v;
 }
 
-// An item's buffers take the vector path when every pointer sits at the same
-// offset m within 16 bytes (diff: the bits in which some source's address
-// differs from dst's) and m is a whole number of elements: the first
-// (16 - m) / size elements, fewer than a vector, are folded one by one and
-// the rest is 16-byte aligned.  Returns that element count (at most count),
-// or kNoVector.
-constexpr uint64_t kNoVector = ~0ull;
-template <class T>
-__device__ __forceinline__ uint64_t item_lead(uintptr_t diff, uintptr_t dst, uint64_t count)
+// Lane l's value of v (l uniform).
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
 {
-    const uintptr_t m = dst & 15u;
-    if ((diff & 15u) != 0 || m % T::kSize != 0) return kNoVector;
-    const uint64_t lead = m == 0 ? 0 : (16 - m) / T::kSize;
-    return lead < count ? lead : count;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// When item_lead finds no vector path but every source sits at one offset m
-// within 16 bytes (sdiff: the bits in which some source's address differs
-// from the first one's, s0) and m is a whole number of elements, the sources
-// still read in vectors after the first (16 - m) / size elements and the
-// output is realigned (split_tile).  Returns that element count, or kNoVector
-// (sources at different offsets, or an item no longer than the lead).
-template <class T>
-__device__ __forceinline__ uint64_t sources_lead(uintptr_t sdiff, uintptr_t s0, uint64_t count)
-{
-    const uintptr_t m = s0 & 15u;
-    if ((sdiff & 15u) != 0 || m % T::kSize != 0) return kNoVector;
-    const uint64_t lead = m == 0 ? 0 : (16 - m) / T::kSize;
-    return lead < count ? lead : kNoVector;
-}
+// One tile of one item, resolved: what its workgroup needs to run it.
+// Uniform over the wavefront.
+enum TilePath : int {
+    kGrid,       // sources at one offset within 16 bytes
+    kOffset,     // sources at different offsets
+    kElems,      // too short for a vector: element by element
+    kNothing,    // a NULL source: the item is skipped
+};
+struct TileDesc {
+    const char *p[8];         // sources 0..7 (valid below nsrc)
+    const char *const *srcs;  // the item's source array
+    char *dst;
+    uint64_t count;
+    uint64_t lt;              // tile within the item
+    int nsrc;
+    uint32_t lead;
+    TilePath path;
+};
 
-// Tile lt (of SUB sub-tiles of kB*kU vectors) of one item.
-template <class T, class Op, int SUB = kSub>
-__device__ void batched_tile(const xred_item &it, uint64_t lt)
+// The rest of a descriptor whose srcs, dst, count, nsrc and lt are set: the
+// source pointers, and how the item is cut (vec_plan).
+template <class T>
+__device__ __forceinline__ void fetch_sources(TileDesc &d)
 {
-    constexpr uint32_t kTileBytes = (uint32_t)kB * kU * SUB * 16u;
-    constexpr uint64_t kTileElems = (uint64_t)kB * kU * SUB * T::kVec;
-    const char *const *sp = (const char *const *)it.srcs;
-    const int nsrc = (int)it.nsrc;
-    uintptr_t diff = 0;   // bits in which some source's address differs from dst's
-    uintptr_t sdiff = 0;  // ... from the first source's
-    const uintptr_t s0 = (uintptr_t)sload(sp);
+    uintptr_t sdiff = 0;   // bits in which some source's address differs from the first's
     bool null_src = false;
-    for (int p = 0; p < nsrc; ++p) {
-        const uintptr_t q = (uintptr_t)sload(sp + p);
-        diff |= q ^ (uintptr_t)it.dst;
-        sdiff |= q ^ s0;
-        null_src |= q == 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        d.p[q] = q < d.nsrc ? sload(d.srcs + q) : nullptr;
+        sdiff |= q < d.nsrc ? (uintptr_t)d.p[q] ^ (uintptr_t)d.p[0] : 0;
+        null_src |= q < d.nsrc && d.p[q] == nullptr;
     }
-    if (null_src) return;
-    char *dst = (char *)it.dst;
-    const GlobalSrc src{sp};
-    const uint64_t count = it.count;
-    uint64_t lead = item_lead<T>(diff, (uintptr_t)dst, count);
-    // the output at another offset than the sources: realigned stores (c > 0)
-    uint32_t c = 0;
-    if (lead == kNoVector) {
-        lead = sources_lead<T>(sdiff, s0, count);
-        if (lead != kNoVector) c = (uint32_t)(((uintptr_t)dst + lead * T::kSize) & 15u);
-        if (c == 0) lead = kNoVector;
+    for (int q = 8; q < d.nsrc; ++q) {
+        const uintptr_t x = (uintptr_t)sload(d.srcs + q);
+        sdiff |= x ^ (uintptr_t)d.p[0];
+        null_src |= x == 0;
     }
-    if (lead != kNoVector) {
-        const size_t lb = (size_t)lead * T::kSize;   // bytes before the first vector
-        const size_t nvec = (count - lead) / T::kVec;
-        const size_t vbytes = nvec * 16;
-        for (int h = 0; h < SUB; ++h) {
-            const size_t off = lt * kTileBytes + (size_t)h * kSubBytes;
-            if (off >= vbytes) break;
-            const Tile tl{lb + off, tile_nrec(vbytes, off, kSubBytes)};
-            if (c != 0) {
-                split_tile<T, Op, 1, kB>(src, nsrc, dst, tl, c);
-                continue;
-            }
-            switch (nsrc) {
-            case 1: reduce_tile<T, Op, 1, kU, kB>(src, nsrc, dst, tl); break;
-            case 2: reduce_tile<T, Op, 2, kU, kB>(src, nsrc, dst, tl); break;
-            case 3: reduce_tile<T, Op, 3, kU, kB>(src, nsrc, dst, tl); break;
-            case 4: reduce_tile<T, Op, 4, kU, kB>(src, nsrc, dst, tl); break;
-            case 5: reduce_tile<T, Op, 5, kU, kB>(src, nsrc, dst, tl); break;
-            case 6: reduce_tile<T, Op, 6, kU, kB>(src, nsrc, dst, tl); break;
-            case 7: reduce_tile<T, Op, 7, kU, kB>(src, nsrc, dst, tl); break;
-            case 8: reduce_tile<T, Op, 8, kU, kB>(src, nsrc, dst, tl); break;
-            // more than 8 sources: the compact group loop (the pipelined
-            // 16/32/64 bodies would raise every batched kernel's register
-            // count and cut its occupancy)
-            default: reduce_tile<T, Op, 0, kU, kB>(src, nsrc, dst, tl); break;
-            }
-        }
-        // the item's first tile also takes the elements before its first
-        // vector, its last tile those after its last full vector
-        reduce_ends<T, Op>(src, nsrc, dst, lt == 0 ? (uint32_t)lead : 0u,
-                           (lt + 1) * kTileElems >= count ? (uint32_t)((count - lead) % T::kVec)
-                                                          : 0u,
-                           lead + nvec * T::kVec);
-    } else if (const uint32_t sl = shift_lead<T>((uintptr_t)dst, count * T::kSize)) {
-        // sources at different offsets: vectors realigned to dst's grid
-        const size_t lb = (size_t)sl * T::kSize;
-        const size_t nvec = (count * T::kSize - lb - 16) / 16, vbytes = nvec * 16;
-        for (int h = 0; h < SUB; ++h) {
-            const size_t off = lt * kTileBytes + (size_t)h * kSubBytes;
-            if (off >= vbytes) break;
-            shift_tile<T, Op, kB>(src, nsrc, dst, lb, off, tile_nrec(vbytes, off, kSubBytes));
-        }
-        reduce_ends<T, Op>(src, nsrc, dst, lt == 0 ? sl : 0u,
-                           (lt + 1) * kTileElems >= count
-                               ? (uint32_t)(count - sl - nvec * T::kVec)
+    const VecPlan vp = vec_plan<T>((uintptr_t)d.p[0], sdiff, (uintptr_t)d.dst, d.count);
+    d.lead = vp.lead;
+    d.path = null_src ? kNothing : !vp.any ? kElems : vp.grid ? kGrid : kOffset;
+}
+
+// Tile lt of item `it` (a descriptor in device memory).
+template <class T>
+__device__ __forceinline__ void fetch_desc(TileDesc &d, const xred_item *it, uint64_t lt)
+{
+    d.lt = lt;
+    d.srcs = (const char *const *)sload(&it->srcs);
+    d.dst = (char *)sload(&it->dst);
+    d.count = sload(&it->count);
+    d.nsrc = (int)sload(&it->nsrc);
+    fetch_sources<T>(d);
+}
+
+// Runs one tile of SUB sub-tiles of kB vectors.  mid() is called once, on the
+// grid path while loads are in flight (the next tile is claimed and resolved
+// there).  EARLY: the loads of the item's ends join the tile's, on its last
+// wavefront, which shortens the chain of a workgroup that runs few tiles
+// (captured batches of 4096 log-uniform items 1375 against 1450 us); a
+// workgroup that runs many folds them after the tile, on its first (queue
+// kernel, 4096 / 619 items: 1250 / 204.4 against 1257 / 206.3 us).
+template <class T, class Op, int SUB, bool EARLY, class Mid>
+__device__ __forceinline__ void run_tile(const TileDesc &d, Mid &&mid)
+{
+    constexpr uint32_t kBytes = (uint32_t)kB * SUB * 16u;
+    const GlobalSrc src{d.srcs};
+    const size_t lb = (size_t)d.lead * T::kSize;   // bytes before the first vector
+    const uint64_t nvec = (d.count - d.lead) / T::kVec;
+    const size_t vbytes = nvec * 16, toff = d.lt * kBytes;
+    // the item's first tile also takes the elements before its first vector,
+    // its last tile those after its last full vector
+    auto ends = [&] {
+        reduce_ends<T, Op>(src, d.nsrc, d.dst, d.lt == 0 ? d.lead : 0u,
+                           (d.lt + 1) * kB * SUB * T::kVec >= d.count
+                               ? (uint32_t)((d.count - d.lead) % T::kVec)
                                : 0u,
-                           sl + nvec * T::kVec);
-    } else {
-        const uint64_t e0 = lt * kTileElems;
-        const uint64_t e1 = count < e0 + kTileElems ? count : e0 + kTileElems;
-        for (uint64_t i = e0 + threadIdx.x; i < e1; i += kB) reduce_elem<T, Op>(src, nsrc, dst, i);
+                           d.lead + nvec * T::kVec, EARLY ? threadIdx.x - (kB - 64) : threadIdx.x);
+    };
+    if (d.path == kGrid) {
+        // groups of 8 sources; sources beyond nsrc get an empty buffer range
+        const uint32_t nrec = toff < vbytes ? tile_nrec(vbytes, toff, kBytes) : 0u;
+        u32x4 in[8][SUB];
+        typename T::Acc acc[SUB][T::kVec];
+        auto load = [&](int q, const char *p, bool on) {
+            const rsrc_t r = make_rsrc((on ? p : d.dst) + lb + toff, on ? nrec : 0u);
+#pragma unroll
+            for (int h = 0; h < SUB; ++h)
+                in[q][h] = bload<kLoadStream>(r, (uint32_t)(h * kB + threadIdx.x) * 16u);
+        };
+#pragma unroll
+        for (int q = 0; q < 8; ++q) load(q, d.p[q], q < d.nsrc);
+        mid();
+        if (EARLY) ends();
+#pragma unroll
+        for (int h = 0; h < SUB; ++h) {
+            up_vec<T>(in[0][h], acc[h]);
+#pragma unroll
+            for (int q = 1; q < 8; ++q)
+                if (q < d.nsrc) fold_vec<T, Op>(acc[h], in[q][h]);
+        }
+        for (int p0 = 8; p0 < d.nsrc; p0 += 8) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const bool on = p0 + q < d.nsrc;
+                load(q, sload(d.srcs + (on ? p0 + q : 0)), on);
+            }
+#pragma unroll
+            for (int h = 0; h < SUB; ++h)
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (p0 + q < d.nsrc) fold_vec<T, Op>(acc[h], in[q][h]);
+        }
+#pragma unroll
+        for (int h = 0; h < SUB; ++h) {
+            if constexpr (__is_same(Op, OpAvg)) {
+#pragma unroll
+                for (int e = 0; e < T::kVec; ++e)
+                    acc[h][e] = avg_scale<T, Op>(acc[h][e], d.nsrc);
+            }
+            store_out(down_vec<T, Op>(acc[h]), d.dst + lb + toff, nrec,
+                      (uint32_t)(h * kB + threadIdx.x) * 16u);
+        }
+        if (!EARLY) ends();
+        return;
     }
+    // one sub-tile at a time
+    auto sub = [&](int h) {
+        const size_t off = toff + (size_t)h * kSubBytes;
+        if (d.path == kElems) {
+            const uint64_t e0 = off / T::kSize;
+            const uint64_t left = d.count > e0 ? d.count - e0 : 0;
+            const uint64_t n = left < kSubBytes / T::kSize ? left : kSubBytes / T::kSize;
+            for (uint64_t i = threadIdx.x; i < n; i += kB)
+                reduce_elem<T, Op>(src, d.nsrc, d.dst, e0 + i);
+        } else if (d.path != kNothing && off < vbytes) {
+            offset_tile<T, Op>(src, d.nsrc, d.dst, lb, off, tile_nrec(vbytes, off, kSubBytes));
+        }
+    };
+    for (int h = 0; h < SUB; ++h) sub(h);
+    if (d.path == kOffset) ends();
+    mid();
 }
 
 template <class T, class Op>
@@ -247,118 +279,39 @@ __global__ __launch_bounds__(kB) void batched_kernel(const xred_item *items, int
     left = uniform64(left);
     while (left > 0 && k < (uint64_t)nitems) {
         k = uniform64(k);
-        const xred_item it = load_item(items, k);
-        const uint64_t nt = item_tiles<T, false>(it);
+        const uint64_t nt = (sload(&items[k].count) + tile_elems<T>() - 1) / tile_elems<T>();
         if (lt >= nt) {
             ++k;
             lt = 0;
             continue;
         }
-        batched_tile<T, Op>(it, lt);
+        TileDesc d;
+        fetch_desc<T>(d, items + k, lt);
+        run_tile<T, Op, kSub, false>(d, [] {});
         ++lt;
         --left;
     }
 }
 
 // ------------------------------------------------------ round-robin variant --
-// Global tile g is processed by workgroup g mod G (G = the workgroups that fit
-// on the chip at once), so the tiles in flight form one moving window over
-// the batch, as in the fused kernel, instead of G scattered ranges.  Each
-// workgroup keeps the batch's tile-start prefix in LDS (copied from the host
-// plan, or computed by a block scan over device-resident descriptors), finds
-// the (item, tile) of each of its tiles by binary search in parallel, and
-// while one tile's loads are in flight fetches the next tile's descriptor and
-// source pointers with scalar loads.
+// Host batches too large for the tile table: global tile g is processed by
+// workgroup g mod G (G = the workgroups that fit on the chip at once), so the
+// tiles in flight form one moving window over the batch, as in the fused
+// kernel, instead of G scattered ranges.  Each workgroup copies the batch's
+// tile-start prefix to LDS, finds the (item, tile) of each of its tiles by
+// binary search in parallel, and while one tile's loads are in flight fetches
+// the next tile's descriptor and source pointers with scalar loads.
 constexpr int kListMax = 1024;     // tiles a workgroup plans per pass
 constexpr int kRrMaxItems = 8192;  // items whose prefix fits the LDS budget
 
-struct TileDesc {
-    const char *p[8];         // sources 0..7 (valid below nsrc)
-    const char *const *srcs;  // the item's source array
-    char *dst;
-    uint64_t count;
-    uint64_t lt;              // tile within the item
-    uint32_t k;               // item
-    int nsrc;
-    uint32_t lead;            // elements before the first vector (0 unless fast)
-    uint32_t c;               // > 0: the output sits c bytes off the sources' vector grid
-    bool fast;                // nsrc <= 8, no NULL source, the sources at one offset in 16 B
-};
-
-template <class T>
-__device__ __forceinline__ void fetch_desc(TileDesc &d, const xred_item *items, uint32_t k,
-                                           uint64_t lt)
-{
-    const xred_item *it = items + k;
-    d.k = k;
-    d.lt = lt;
-    d.srcs = (const char *const *)sload(&it->srcs);
-    d.dst = (char *)sload(&it->dst);
-    d.count = sload(&it->count);
-    d.nsrc = (int)sload(&it->nsrc);
-    uintptr_t diff = 0, sdiff = 0;
-    bool null_src = false;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        d.p[q] = q < d.nsrc ? sload(d.srcs + q) : nullptr;
-        diff |= q < d.nsrc ? (uintptr_t)d.p[q] ^ (uintptr_t)d.dst : 0;
-        sdiff |= q < d.nsrc ? (uintptr_t)d.p[q] ^ (uintptr_t)d.p[0] : 0;
-        null_src |= q < d.nsrc && d.p[q] == nullptr;
-    }
-    uint64_t lead = item_lead<T>(diff, (uintptr_t)d.dst, d.count);
-    d.c = 0;
-    if (lead == kNoVector) {
-        // the sources at one offset, the output at another: realigned stores
-        const uint64_t sl = sources_lead<T>(sdiff, (uintptr_t)d.p[0], d.count);
-        const uint32_t c =
-            sl != kNoVector ? (uint32_t)(((uintptr_t)d.dst + sl * T::kSize) & 15u) : 0u;
-        if (c != 0) {
-            lead = sl;
-            d.c = c;
-        }
-    }
-    d.fast = d.nsrc <= 8 && !null_src && lead != kNoVector;
-    d.lead = d.fast ? (uint32_t)lead : 0u;
-}
-
-// Sub-tile h of a straight-line tile whose vectors start at byte `off` of
-// d's output (nrec bytes of the tile exist): one aligned vector per thread,
-// or realigned stores when the output sits d.c bytes off the sources' grid.
-__device__ __forceinline__ void tile_store(u32x4 v, rsrc_t w, const TileDesc &d, size_t off,
-                                           uint32_t nrec, int h)
-{
-    if (d.c == 0) {
-        bstore<kStoreOut>(v, w, (uint32_t)(h * kB + threadIdx.x) * 16u);
-        return;
-    }
-    const uint32_t start = (uint32_t)h * kSubBytes;
-    if (start >= nrec) return;
-    const uint32_t left = nrec - start;
-    split_store(v, d.dst + off + start, left < kSubBytes ? left : kSubBytes, d.c);
-}
-
-template <class T, class Op, bool PLANNED>
+template <class T, class Op>
 __global__ __launch_bounds__(kB) void batched_rr_kernel(const xred_item *items, int nitems,
                                                         const uint32_t *tile_start)
 {
     extern __shared__ uint2 s_dyn[];
-    __shared__ uint64_t s_scan[kB];
     uint2 *s_list = s_dyn;                             // kListMax entries
     uint32_t *s_pre = (uint32_t *)(s_dyn + kListMax);  // nitems + 1 entries
-    if constexpr (PLANNED) {
-        for (int i = threadIdx.x; i <= nitems; i += kB) s_pre[i] = tile_start[i];
-    } else {
-        uint64_t base = 0;
-        for (int w0 = 0; w0 < nitems; w0 += kB) {
-            const int i = w0 + (int)threadIdx.x;
-            const uint64_t c = i < nitems ? item_tiles<T, true>(items[i]) : 0;
-            const uint64_t incl = block_inclusive_scan(c, s_scan);
-            if (i < nitems) s_pre[i] = (uint32_t)(base + incl - c);
-            base += s_scan[kB - 1];
-        }
-        if (base >= 0xFFFFFFFFull) return;   // more tiles than the plan can index: run nothing
-        if (threadIdx.x == 0) s_pre[nitems] = (uint32_t)base;
-    }
+    for (int i = threadIdx.x; i <= nitems; i += kB) s_pre[i] = tile_start[i];
     __syncthreads();
     const uint64_t total = s_pre[nitems];
     const uint64_t G = gridDim.x;
@@ -376,64 +329,16 @@ __global__ __launch_bounds__(kB) void batched_rr_kernel(const xred_item *items, 
             s_list[j] = uint2{(uint32_t)lo, (uint32_t)(g - s_pre[lo])};
         }
         __syncthreads();
+        auto fetch = [&](TileDesc &d, int j) {
+            fetch_desc<T>(d, items + __builtin_amdgcn_readfirstlane(s_list[j].x),
+                          __builtin_amdgcn_readfirstlane(s_list[j].y));
+        };
         TileDesc cur, nxt;
-        fetch_desc<T>(cur, items, __builtin_amdgcn_readfirstlane(s_list[0].x),
-                   __builtin_amdgcn_readfirstlane(s_list[0].y));
+        fetch(cur, 0);
         for (int j = 0; j < n; ++j) {
-            // Issue the current tile's loads.  Straight-line code: sources
-            // beyond nsrc, and tiles not on the fast path, get a zero-length
-            // buffer range, so their loads return 0 without touching memory
-            // and their store is dropped.
-            const size_t lb = (size_t)cur.lead * T::kSize;
-            const size_t nvec = (cur.count - cur.lead) / T::kVec;
-            const size_t vbytes = nvec * 16, toff = cur.lt * kTileBytes;
-            const uint32_t nrec = cur.fast && toff < vbytes ? tile_nrec(vbytes, toff, kTileBytes) : 0u;
-            u32x4 in[8][kSub];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool on = q < cur.nsrc;
-                const rsrc_t r = make_rsrc((on ? cur.p[q] : cur.dst) + lb + toff, on ? nrec : 0u);
-#pragma unroll
-                for (int h = 0; h < kSub; ++h)
-                    in[q][h] = bload<kLoadStream>(r, (uint32_t)(h * kB + threadIdx.x) * 16u);
-            }
-            // fetch the next tile's descriptor while those loads are in flight
-            if (j + 1 < n)
-                fetch_desc<T>(nxt, items, __builtin_amdgcn_readfirstlane(s_list[j + 1].x),
-                           __builtin_amdgcn_readfirstlane(s_list[j + 1].y));
-            // fold (unused sources skipped by a uniform select) and store
-            const rsrc_t w = make_rsrc(cur.dst + lb + toff, nrec);
-#pragma unroll
-            for (int h = 0; h < kSub; ++h) {
-                typename T::Acc acc[T::kVec];
-                up_vec<T>(in[0][h], acc);
-#pragma unroll
-                for (int q = 1; q < 8; ++q) {
-                    const bool on = q < cur.nsrc;
-                    typename T::Acc b[T::kVec];
-                    up_vec<T>(in[q][h], b);
-#pragma unroll
-                    for (int e = 0; e < T::kVec; ++e) {
-                        const typename T::Acc c = combine<T, Op>(acc[e], b[e]);
-                        acc[e] = on ? c : acc[e];
-                    }
-                }
-                if constexpr (__is_same(Op, OpAvg)) {
-#pragma unroll
-                    for (int e = 0; e < T::kVec; ++e) acc[e] = avg_scale<T, Op>(acc[e], cur.nsrc);
-                }
-                tile_store(down_vec<T, Op>(acc), w, cur, lb + toff, nrec, h);
-            }
-            if (cur.fast) {
-                reduce_ends<T, Op>(GlobalSrc{cur.srcs}, cur.nsrc, cur.dst,
-                                   cur.lt == 0 ? cur.lead : 0u,
-                                   (cur.lt + 1) * tile_elems<T>() >= cur.count
-                                       ? (uint32_t)((cur.count - cur.lead) % T::kVec)
-                                       : 0u,
-                                   cur.lead + nvec * T::kVec);
-            } else {
-                batched_tile<T, Op>(load_item(items, cur.k), cur.lt);
-            }
+            run_tile<T, Op, kSub, false>(cur, [&] {
+                if (j + 1 < n) fetch(nxt, j + 1);
+            });
             cur = nxt;
             // the waves start every tile together (8 items of 32M bf16 per
             // source: 5.18 against 4.99 TB/s; 64 items of 4M: 4.90 against 4.98)
@@ -445,16 +350,21 @@ __global__ __launch_bounds__(kB) void batched_rr_kernel(const xred_item *items, 
 
 // ------------------------------------------------------------ queue variant --
 // Device descriptors (the host never sees the sizes): a persistent grid takes
-// the batch's tiles in order from a counter in device memory, one tile per
-// claim, so the tiles in flight stay one compact window over the batch, as
-// when the hardware dispatches one workgroup per tile of a host-built table,
-// and no workgroup keeps a fixed share of the batch.  Each workgroup first
-// scans the tile counts of all items into an LDS tile-start prefix (its first
-// claim in flight meanwhile).  Per tile it claims the next tile and issues
-// this tile's loads; while they are in flight, the claim's answer is handed
-// to all waves through LDS and every wave finds the next tile's item (a
-// 64-ary search of the prefix) and fetches its descriptor and source
+// the batch's tiles in order, so the tiles in flight stay one compact window
+// over the batch, as when the hardware dispatches one workgroup per tile of a
+// host-built table, and no workgroup keeps a fixed share of the batch.  Each
+// workgroup scans the tile counts of all items into an LDS tile-start prefix;
+// its first unit of tiles is its own index, later ones come from a counter in
+// device memory.  While a tile's loads are in flight, the next unit's claim
+// is handed to all waves through LDS and every wave finds the next tile's item
+// (a 64-ary search of the prefix) and fetches its descriptor and source
 // pointers, so the next tile's loads follow this tile's stores at once.
+//
+// The counter answers one claim in about 14 ns.  A unit is therefore as many
+// tiles as it takes to move kClaimBytes (most tiles of a batch of small items
+// are far from full), and a batch of at most one unit per workgroup claims
+// nothing.  With one claim per tile, the first included, P=4 bf16 items of
+// 8-16 KiB took 17.6 us for 563 (16.8 now), 66 of 8-128 KiB 10.4 us (6.5).
 //
 // What was measured on the 4096-item log-uniform batch (MI355X, same box):
 // one workgroup of 512 threads per CU and tiles of two 512-vector sub-tiles
@@ -479,7 +389,8 @@ struct QueueCtl {
     uint64_t *finished;
 };
 constexpr int kQMaxItems = 16384;   // items whose 32-bit tile-start prefix fits in LDS
-constexpr int kQSub = 2;            // 512-vector sub-tiles per claimed tile
+constexpr float kClaimBytes = 96 << 10;   // 14 ns at 6.9 TB/s
+constexpr uint32_t kClaimMost = 8;        // tiles per unit
 
 // The item k < n holding tile g: the last k with pre[k] <= g (pre[0] = 0 <= g,
 // pre non-decreasing).  Each level reads one prefix entry per lane and keeps
@@ -511,35 +422,28 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <class T, class Op, int SUB>
+template <class T, class Op>
 __global__ __launch_bounds__(kB) void batched_queue_kernel(const xred_item *items, int nitems,
                                                            QueueCtl q)
 {
-    constexpr uint32_t kTileBytes = (uint32_t)kB * SUB * 16u;
-    constexpr uint64_t kTileElems = (uint64_t)kB * SUB * T::kVec;
-    auto tiles_of = [](const xred_item &it) -> uint64_t {
-        return item_runnable(it) ? (it.count + kTileElems - 1) / kTileElems : 0;
-    };
     auto claim = [&q]() -> uint64_t {
         return __hip_atomic_fetch_add(q.next, (uint64_t)1, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
     };
     extern __shared__ uint32_t s_pre[];   // nitems + 1 tile starts, in the occupancy reservation
-    __shared__ uint64_t s_wave[kB / 64];
-    // The claim made during tile b is written to s_claim[b % 2] at the
-    // tile's end and read after its barrier; the slot's previous claim was
-    // read before the barrier that precedes the write.
+    __shared__ uint64_t s_wave[2 * kB / 64];
+    // The claim made during a tile is written to s_claim[b % 2], b counting
+    // the claims, and read after the tile's barrier; the slot's previous claim
+    // was read before the barrier that precedes the write.
     __shared__ uint64_t s_claim[2];
     if (q.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(q.clear, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t c0 = 0;
-    if (threadIdx.x == 0) c0 = claim();   // in flight while the workgroup scans
     // tile counts of this thread's consecutive items (four descriptor loads
     // in flight at a time), kept in the prefix's place; then the
     // workgroup's exclusive scan turns them into tile starts
     const int per = (nitems + kB - 1) / kB;
     const int i0 = min(nitems, (int)threadIdx.x * per), i1 = min(nitems, i0 + per);
-    uint64_t mine = 0;
+    uint64_t mine = 0, bytes = 0;
     for (int j = i0; j < i1; j += 4) {
         xred_item it[4];
 #pragma unroll
@@ -548,14 +452,15 @@ __global__ __launch_bounds__(kB) void batched_queue_kernel(const xred_item *item
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (j + u < i1) {
-                const uint64_t t = tiles_of(it[u]);
+                const uint64_t t = item_tiles<T>(it[u]);
                 mine += t;
+                if (t != 0) bytes += it[u].count * T::kSize * (it[u].nsrc + 1);
                 s_pre[j + u] = t < 0xFFFFFFFFull ? (uint32_t)t : 0xFFFFFFFFu;
             }
         }
     }
     uint64_t total = 0;
-    uint64_t run = block_exclusive_scan(mine, s_wave, &total);
+    uint64_t run = block_exclusive_scan(mine, bytes, s_wave, &total, &bytes);
     for (int i = i0; i < i1; ++i) {
         const uint32_t t = s_pre[i];
         s_pre[i] = (uint32_t)run;
@@ -563,84 +468,44 @@ __global__ __launch_bounds__(kB) void batched_queue_kernel(const xred_item *item
     }
     total = uniform64(total);
     if (total > 0xFFFFFFFFull) total = 0;   // more tiles than the prefix indexes: run nothing
-    if (threadIdx.x == 0) {
-        s_pre[nitems] = (uint32_t)total;
-        s_claim[1] = c0;
-    }
+    if (threadIdx.x == 0) s_pre[nitems] = (uint32_t)total;
     __syncthreads();
-    uint64_t g = uniform64(s_claim[1]);
+    // tiles per unit, the same in every workgroup; one while there are fewer
+    // than eight per workgroup (units of two end 563 one-tile items a round later)
+    const uint32_t G = gridDim.x;
+    const float want = __builtin_ceilf((float)total * kClaimBytes / (float)bytes);
+    uint32_t unit = want < (float)kClaimMost ? (uint32_t)want : kClaimMost;
+    unit = min(unit, (uint32_t)total / (4 * G));
+    unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)max(unit, 1u));
+    const bool dynamic = total > (uint64_t)unit * G;
+    uint64_t g = (uint64_t)blockIdx.x * unit;   // the tile being run
+    uint32_t left = unit;                       // tiles of its unit, itself included
     TileDesc cur{};
-    if (g < total) {
-        const int k = find_item(s_pre, nitems, (uint32_t)g);
-        fetch_desc<T>(cur, items, (uint32_t)k, uniform64(g - s_pre[k]));
-    }
-    for (int b = 0; g < total; ++b) {
+    auto fetch = [&](TileDesc &d, uint64_t t) {
+        const int k = find_item(s_pre, nitems, (uint32_t)t);
+        fetch_desc<T>(d, items + k, uniform64(t - s_pre[k]));
+    };
+    if (g < total) fetch(cur, g);
+    for (uint32_t b = 0; g < total;) {
+        const bool refill = dynamic && left == 1;
         uint64_t c = 0;
-        if (threadIdx.x == 0) c = claim();   // answered while this tile streams
-        // straight-line tile: sources beyond nsrc, and tiles off the fast
-        // path, get a zero-length buffer range
-        const size_t lb = (size_t)cur.lead * T::kSize;
-        const size_t nvec = (cur.count - cur.lead) / T::kVec;
-        const size_t vbytes = nvec * 16, toff = cur.lt * kTileBytes;
-        const uint32_t nrec = cur.fast && toff < vbytes ? tile_nrec(vbytes, toff, kTileBytes) : 0u;
-        u32x4 in[8][SUB];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const bool on = p < cur.nsrc;
-            const rsrc_t r = make_rsrc((on ? cur.p[p] : cur.dst) + lb + toff, on ? nrec : 0u);
-#pragma unroll
-            for (int h = 0; h < SUB; ++h)
-                in[p][h] = bload<kLoadStream>(r, (uint32_t)(h * kB + threadIdx.x) * 16u);
-        }
-        // With this tile's loads in flight, hand the claim to every wave
-        // and fetch the next tile's descriptor and source pointers, so the
-        // next tile's loads can be issued as soon as this tile is stored.
-        if (threadIdx.x == 0) s_claim[b & 1] = c;
-        lds_barrier();
-        const uint64_t gn = uniform64(s_claim[b & 1]);
+        if (refill && threadIdx.x == 0) c = claim();   // answered while this tile streams
+        uint64_t gn = left == 1 ? total : g + 1;
         TileDesc nxt{};
-        if (gn < total) {
-            const int k = find_item(s_pre, nitems, (uint32_t)gn);
-            fetch_desc<T>(nxt, items, (uint32_t)k, uniform64(gn - s_pre[k]));
-        }
-        const rsrc_t w = make_rsrc(cur.dst + lb + toff, nrec);
-#pragma unroll
-        for (int h = 0; h < SUB; ++h) {
-            typename T::Acc acc[T::kVec];
-            up_vec<T>(in[0][h], acc);
-#pragma unroll
-            for (int p = 1; p < 8; ++p) {
-                const bool on = p < cur.nsrc;
-                typename T::Acc x[T::kVec];
-                up_vec<T>(in[p][h], x);
-#pragma unroll
-                for (int e = 0; e < T::kVec; ++e) {
-                    const typename T::Acc cmb = combine<T, Op>(acc[e], x[e]);
-                    acc[e] = on ? cmb : acc[e];
-                }
-            }
-            if constexpr (__is_same(Op, OpAvg)) {
-#pragma unroll
-                for (int e = 0; e < T::kVec; ++e) acc[e] = avg_scale<T, Op>(acc[e], cur.nsrc);
-            }
-            tile_store(down_vec<T, Op>(acc), w, cur, lb + toff, nrec, h);
-        }
-        if (cur.fast) {
-            reduce_ends<T, Op>(GlobalSrc{cur.srcs}, cur.nsrc, cur.dst,
-                               cur.lt == 0 ? cur.lead : 0u,
-                               (cur.lt + 1) * kTileElems >= cur.count
-                                   ? (uint32_t)((cur.count - cur.lead) % T::kVec)
-                                   : 0u,
-                               cur.lead + nvec * T::kVec);
-        } else {
-            batched_tile<T, Op, SUB>(load_item(items, cur.k), cur.lt);
-        }
+        run_tile<T, Op, kSub, false>(cur, [&] {
+            if (refill && threadIdx.x == 0) s_claim[b & 1] = c;
+            lds_barrier();   // also keeps the waves on one tile
+            if (refill) gn = (G + uniform64(s_claim[b & 1])) * unit;
+            if (gn < total) fetch(nxt, gn);
+        });
+        b += refill;
+        left = left == 1 ? unit : left - 1;
         cur = nxt;
         g = gn;
     }
     // every claim of this workgroup has been answered (each was read back
     // above), so the last workgroup's reset is the counter's last write
-    if (q.finished != nullptr && threadIdx.x == 0) {
+    if (q.finished != nullptr && dynamic && threadIdx.x == 0) {
         const uint64_t n = __hip_atomic_fetch_add(q.finished, (uint64_t)1, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
         if (n + 1 == gridDim.x) {
@@ -671,148 +536,18 @@ __global__ __launch_bounds__(kB) void batched_queue_kernel(const xred_item *item
 // workgroups per CU.
 // Under a CU budget the grid is smaller and each workgroup strides over the
 // table.
-constexpr int kTB = 512;
+constexpr int kTB = kB;
 constexpr int kTableSub = 1;          // 16-byte vectors per thread and source
 constexpr int kTableWgsPerCu = 2;
 
 template <class T>
 constexpr uint64_t table_tile_elems() { return (uint64_t)kTB * kTableSub * T::kVec; }
 
-// The fields of a descriptor a tile needs, loaded with scalar loads.
-struct ItemHead {
-    const char *const *srcs;
-    char *dst;
-    uint64_t count;
-    int nsrc;
-};
-
-__device__ __forceinline__ ItemHead load_head(const xred_item *it)
-{
-    return ItemHead{(const char *const *)sload(&it->srcs), (char *)sload(&it->dst),
-                    sload(&it->count), (int)sload(&it->nsrc)};
-}
-
-// Tile lt (of kTB * kTableSub vectors) of the item with header h.  CHECK: the descriptor is the
-// caller's device memory, so an item with a NULL source pointer is skipped
-// (the host validates its own descriptors before staging them).
-template <class T, class Op, bool CHECK>
-__device__ __forceinline__ void table_tile(const ItemHead &h, uint64_t lt)
-{
-    constexpr int U = kTableSub;
-    constexpr uint32_t kBytes = (uint32_t)kTB * U * 16u;
-    const char *const *srcs = h.srcs;
-    char *dst = h.dst;
-    const uint64_t count = h.count;
-    const int nsrc = h.nsrc;
-    const GlobalSrc src{srcs};
-    const size_t toff = lt * kBytes;
-    const char *p[8];
-    uintptr_t diff = 0;   // bits in which some source's address differs from dst's
-    bool null_src = false;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        p[q] = q < nsrc ? sload(srcs + q) : nullptr;
-        diff |= q < nsrc ? (uintptr_t)p[q] ^ (uintptr_t)dst : 0;
-        null_src |= q < nsrc && p[q] == nullptr;
-    }
-    uint64_t lead = item_lead<T>(diff, (uintptr_t)dst, count);
-    if (nsrc > 8 || lead == kNoVector) {
-        // the general tile: any source count, element-aligned buffers
-        uintptr_t all = 0, sdiff = 0;
-        const uintptr_t s0 = (uintptr_t)p[0];
-        for (int q = 0; q < nsrc; ++q) {
-            const uintptr_t x = (uintptr_t)sload(srcs + q);
-            all |= x ^ (uintptr_t)dst;
-            sdiff |= x ^ s0;
-            null_src |= x == 0;
-        }
-        if (CHECK && null_src) return;
-        lead = item_lead<T>(all, (uintptr_t)dst, count);
-        uint32_t c = 0;   // > 0: the output at another offset than the sources
-        if (lead == kNoVector) {
-            lead = sources_lead<T>(sdiff, s0, count);
-            if (lead != kNoVector) c = (uint32_t)(((uintptr_t)dst + lead * T::kSize) & 15u);
-            if (c == 0) lead = kNoVector;
-        }
-        if (lead != kNoVector) {
-            const size_t nvec = (count - lead) / T::kVec, vbytes = nvec * 16;
-            const Tile tl{(size_t)lead * T::kSize + toff, tile_nrec(vbytes, toff, kBytes)};
-            if (toff < vbytes) {
-                if (c != 0) split_tile<T, Op, 1, kTB>(src, nsrc, dst, tl, c);
-                else reduce_tile<T, Op, 0, U, kTB>(src, nsrc, dst, tl);
-            }
-        } else if (const uint32_t sl = shift_lead<T>((uintptr_t)dst, count * T::kSize)) {
-            // sources at different offsets: vectors realigned to dst's grid
-            const size_t lb = (size_t)sl * T::kSize;
-            const size_t nvec = (count * T::kSize - lb - 16) / 16, vbytes = nvec * 16;
-            if (toff < vbytes)
-                shift_tile<T, Op, kTB>(src, nsrc, dst, lb, toff, tile_nrec(vbytes, toff, kBytes));
-            reduce_ends<T, Op>(src, nsrc, dst, lt == 0 ? sl : 0u,
-                               (lt + 1) * table_tile_elems<T>() >= count
-                                   ? (uint32_t)(count - sl - nvec * T::kVec)
-                                   : 0u,
-                               sl + nvec * T::kVec);
-            return;
-        } else {
-            const uint64_t e0 = lt * table_tile_elems<T>();
-            const uint64_t e1 =
-                count < e0 + table_tile_elems<T>() ? count : e0 + table_tile_elems<T>();
-            for (uint64_t i = e0 + threadIdx.x; i < e1; i += kTB)
-                reduce_elem<T, Op>(src, nsrc, dst, i);
-            return;
-        }
-    } else {
-        if (CHECK && null_src) return;
-        // straight-line tile: sources beyond nsrc get a zero-length range
-        const size_t lb = (size_t)lead * T::kSize;
-        const size_t vbytes = (count - lead) / T::kVec * 16;
-        const uint32_t nrec = toff < vbytes ? tile_nrec(vbytes, toff, kBytes) : 0u;
-        u32x4 in[8][U];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const bool on = q < nsrc;
-            const rsrc_t r = make_rsrc((on ? p[q] : dst) + lb + toff, on ? nrec : 0u);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                in[q][u] = bload<kLoadStream>(r, (uint32_t)(u * kTB + threadIdx.x) * 16u);
-        }
-        const rsrc_t w = make_rsrc(dst + lb + toff, nrec);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            typename T::Acc acc[T::kVec];
-            up_vec<T>(in[0][u], acc);
-#pragma unroll
-            for (int q = 1; q < 8; ++q) {
-                const bool on = q < nsrc;
-                typename T::Acc b[T::kVec];
-                up_vec<T>(in[q][u], b);
-#pragma unroll
-                for (int e = 0; e < T::kVec; ++e) {
-                    const typename T::Acc c = combine<T, Op>(acc[e], b[e]);
-                    acc[e] = on ? c : acc[e];
-                }
-            }
-            if constexpr (__is_same(Op, OpAvg)) {
-#pragma unroll
-                for (int e = 0; e < T::kVec; ++e) acc[e] = avg_scale<T, Op>(acc[e], nsrc);
-            }
-            bstore<kStoreOut>(down_vec<T, Op>(acc), w, (uint32_t)(u * kTB + threadIdx.x) * 16u);
-        }
-    }
-    // the item's first tile also takes the elements before its first vector,
-    // its last tile those after its last full vector
-    reduce_ends<T, Op>(src, nsrc, dst, lt == 0 ? (uint32_t)lead : 0u,
-                       (lt + 1) * table_tile_elems<T>() >= count
-                           ? (uint32_t)((count - lead) % T::kVec)
-                           : 0u,
-                       lead + (count - lead) / T::kVec * T::kVec);
-}
-
 // NARROW: the table holds 16-bit item indices (batches of at most 65536
 // items), two per 32-bit word, little-endian; the word is loaded whole (the
 // table is padded to 8 bytes) so every scalar load stays dword-aligned.
 template <class T, class Op, bool NARROW>
-__global__ __launch_bounds__(kTB) void batched_table_kernel(const xred_item *items,
+__global__ __launch_bounds__(kTB, kTableWgsPerCu * kTB / 256) void batched_table_kernel(const xred_item *items,
                                                             const uint32_t *table,
                                                             uint64_t ntiles)
 {
@@ -826,8 +561,9 @@ __global__ __launch_bounds__(kTB) void batched_table_kernel(const xred_item *ite
         } else {
             k = sload(&table[g]);
         }
-        const xred_item *it = items + k;
-        table_tile<T, Op, false>(load_head(it), g - sload(&it->reserved));
+        TileDesc d;
+        fetch_desc<T>(d, items + k, g - sload(&items[k].reserved));
+        run_tile<T, Op, kTableSub, true>(d, [] {});
     }
 }
 
@@ -857,113 +593,76 @@ hipError_t batched_table_group(xred_dtype dtype, xred_op op, const xred_item *d_
     });
 }
 
-// ---------------------------------------------------------- grouped variant --
-// Device descriptors (the host cannot see the sizes, so it cannot list the
-// tiles): the batch is cut into `ngroups` runs of consecutive items, run q
-// gets its own `m` workgroups (blockIdx m*q .. m*q+m-1), and tile j of the
-// run goes to the run's workgroup j mod m.  The m workgroups of a run walk
-// its tiles side by side, so the tiles in flight stay one compact window, as
-// in the tile-table kernel; and since the workgroups of later runs are
-// dispatched in order as earlier ones retire, no workgroup keeps a fixed
-// share of the whole batch (a persistent grid ends with its slowest
-// workgroup).  Each workgroup scans its run's descriptors into an LDS
-// tile-start prefix, lists its own tiles (item, tile) by binary search, and
-// runs the tile-table kernel's tile on each, with a barrier after every tile
-// so the workgroup's waves read one tile together (c4: 5.7 against 5.45 TB/s
-// with the waves left to drift apart).  No state is kept between calls,
-// so the launch can be captured in a graph.  With fewer workgroups than
-// m * ngroups (a CU budget), each set of m workgroups strides over the runs.
-constexpr int kGrpMaxItems = 2048;          // items per run (LDS prefix)
-constexpr int kGrpPerThread = kGrpMaxItems / kTB;
-constexpr size_t kGrpLdsBytes =
-    sizeof(uint64_t) * (kGrpMaxItems + 1 + kTB + kTB / 64) + sizeof(uint32_t) * kTB;
-
-template <class T>
-__device__ __forceinline__ uint64_t table_item_tiles(const xred_item &it)
-{
-    if (!item_runnable(it)) return 0;
-    return (it.count + table_tile_elems<T>() - 1) / table_tile_elems<T>();
-}
+// ------------------------------------------------------------- runs variant --
+// Device descriptors without state between calls, so that the launch can be
+// captured in a graph: the batch is cut into runs of up to 64 consecutive
+// items, run r gets its own m workgroups (blockIdx m*r .. m*r+m-1), and tile j
+// of the run goes to the run's workgroup j mod m.  The m workgroups of a run
+// walk its tiles side by side, so the tiles in flight stay one compact
+// window; and since the workgroups of later runs are dispatched in order as
+// earlier ones retire, no workgroup keeps a fixed share of the whole batch.
+// Every wave holds the run's descriptors, one item per lane, and finds its
+// tiles with a scan, a ballot and readlanes: one memory latency and no LDS
+// before the first source pointers are fetched.  (Against scanning into LDS
+// and listing tiles by binary search, bf16 sum: P=8 items of 8 KiB-1 MiB, 4096 /
+// 619 of them 1652 / 273 -> 1366 / 220 us; 563 items of 8-16 KiB 53 -> 17; P=16
+// 3000 items 774 -> 444; and against one persistent grid of the same tiles for
+// up to 64 items: 12 items 6.5 -> 5.0 us, 64 of 8 MiB 860 -> 855.)  Two
+// workgroups per CU of 8 KiB tiles are within 2 % on large batches and lose
+// 15 % on 64 large items.  With fewer workgroups than m * nruns (a CU budget),
+// each set of m workgroups strides over the runs.
+constexpr int kRunItems = 64;      // one per lane
+constexpr int kRunsWgsPerCu = 1;
 
 template <class T, class Op>
-__global__ __launch_bounds__(kTB) void batched_grouped_kernel(const xred_item *items, int nitems,
-                                                              uint32_t ngroups, uint32_t m)
+__global__ __launch_bounds__(kB) void batched_runs_kernel(const xred_item *items, int nitems,
+                                                          uint32_t nruns, uint32_t m)
 {
-    extern __shared__ uint64_t s_grp[];          // the occupancy reservation, partly used
-    uint64_t *s_pre = s_grp;                     // kGrpMaxItems + 1 tile starts
-    uint64_t *s_lt = s_pre + kGrpMaxItems + 1;   // kTB tiles within their item
-    uint64_t *s_wave = s_lt + kTB;               // kTB / 64 wave sums
-    uint32_t *s_item = (uint32_t *)(s_wave + kTB / 64);   // kTB items within the run
+    extern __shared__ char occupancy_reservation[];
+    (void)occupancy_reservation;
+    const int lane = (int)(threadIdx.x & 63);
     const uint32_t w = blockIdx.x % m;
     const uint32_t sets = gridDim.x / m;
-    for (uint32_t q = blockIdx.x / m; q < ngroups; q += sets) {
-        const int i0 = (int)((uint64_t)nitems * q / ngroups);
-        const int n = (int)((uint64_t)nitems * (q + 1) / ngroups) - i0;   // <= kGrpMaxItems
-        // tile counts of the run's items, kGrpPerThread consecutive items per thread
-        uint64_t c[kGrpPerThread], mine = 0;
-#pragma unroll
-        for (int j = 0; j < kGrpPerThread; ++j) {
-            const int i = (int)threadIdx.x * kGrpPerThread + j;
-            c[j] = i < n ? table_item_tiles<T>(items[i0 + i]) : 0;
-            mine += c[j];
+    for (uint32_t r = blockIdx.x / m; r < nruns; r += sets) {
+        const int i0 = (int)r * kRunItems;
+        const int n = min(kRunItems, nitems - i0);
+        const xred_item it = items[i0 + min(lane, n - 1)];
+        const uint64_t tiles = lane < n ? item_tiles<T>(it) : 0;
+        const uint64_t upto = wave_inclusive_scan(tiles);
+        const uint64_t total = readlane64(upto, 63);
+        for (uint64_t g = w; g < total; g += m) {
+            const int k = __popcll(__ballot(upto <= g));   // the first item past tile g
+            TileDesc d;
+            d.lt = g - readlane64(upto - tiles, k);
+            d.srcs = (const char *const *)readlane64((uint64_t)it.srcs, k);
+            d.dst = (char *)readlane64((uint64_t)it.dst, k);
+            d.count = readlane64(it.count, k);
+            d.nsrc = __builtin_amdgcn_readlane((int)it.nsrc, k);
+            fetch_sources<T>(d);
+            run_tile<T, Op, kSub, true>(d, [] {});
+            __builtin_amdgcn_s_barrier();   // the waves start every tile together
         }
-        uint64_t total = 0;
-        uint64_t run = block_exclusive_scan(mine, s_wave, &total);
-#pragma unroll
-        for (int j = 0; j < kGrpPerThread; ++j) {
-            const int i = (int)threadIdx.x * kGrpPerThread + j;
-            if (i < n) s_pre[i] = run;
-            run += c[j];
-        }
-        if (threadIdx.x == 0) s_pre[n] = total;
-        __syncthreads();
-        // this workgroup's tiles are w, w + m, w + 2m, ... below total
-        for (uint64_t g0 = w; g0 < total; g0 += (uint64_t)kTB * m) {
-            const uint64_t left = (total - g0 + m - 1) / m;
-            const int cnt = left < (uint64_t)kTB ? (int)left : kTB;
-            if ((int)threadIdx.x < cnt) {
-                const uint64_t g = g0 + (uint64_t)threadIdx.x * m;
-                int lo = 0, hi = n;   // s_pre[lo] <= g < s_pre[hi]
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_pre[mid] <= g) lo = mid;
-                    else hi = mid;
-                }
-                s_item[threadIdx.x] = (uint32_t)lo;
-                s_lt[threadIdx.x] = g - s_pre[lo];
-            }
-            __syncthreads();
-            for (int j = 0; j < cnt; ++j) {
-                const uint32_t k = __builtin_amdgcn_readfirstlane(s_item[j]);
-                table_tile<T, Op, true>(load_head(items + i0 + k), uniform64(s_lt[j]));
-                __syncthreads();   // the waves start every tile together
-            }
-            __syncthreads();   // the list is rewritten next
-        }
-        __syncthreads();       // the prefix is rewritten next
     }
 }
 
 template <class T, class Op>
-hipError_t go_grouped(const xred_item *d_items, int nitems, uint32_t ngroups, uint32_t m,
-                      unsigned grid, int wgs_per_cu, hipStream_t s)
+hipError_t go_runs(const xred_item *d_items, int nitems, uint32_t nruns, uint32_t m, unsigned grid,
+                   hipStream_t s)
 {
-    size_t lds = (size_t)(lds_per_cu() / wgs_per_cu) / 512 * 512 - 512;
-    if (lds < kGrpLdsBytes) lds = kGrpLdsBytes;
-    return launch_kernel(batched_grouped_kernel<T, Op>, dim3(grid), dim3(kTB), lds, s, d_items,
-                         nitems, ngroups, m);
+    const size_t lds = (size_t)(lds_per_cu() / kRunsWgsPerCu) / 512 * 512 - 512;
+    return launch_kernel(batched_runs_kernel<T, Op>, dim3(grid), dim3(kB), lds, s, d_items, nitems,
+                         nruns, m);
 }
 
-// Grouped launcher for the element types Ts.
+// Runs launcher for the element types Ts.
 template <class... Ts>
-hipError_t batched_grouped_group(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                 int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                 int wgs_per_cu, hipStream_t s)
+hipError_t batched_runs_group(xred_dtype dtype, xred_op op, const xred_item *d_items, int nitems,
+                              uint32_t nruns, uint32_t m, unsigned grid, hipStream_t s)
 {
     return with_dtype_among<Ts...>(dtype, [&](auto t) {
         using T = decltype(t);
         return with_op<T, true>(op, [&](auto o) {
-            return go_grouped<T, decltype(o)>(d_items, nitems, ngroups, m, grid, wgs_per_cu, s);
+            return go_runs<T, decltype(o)>(d_items, nitems, nruns, m, grid, s);
         });
     });
 }
@@ -975,7 +674,7 @@ hipError_t go_queue(const xred_item *d_items, int nitems, QueueCtl q, unsigned g
     size_t lds = (size_t)(lds_per_cu() / wgs_per_cu) / 512 * 512 - 512;
     const size_t need = sizeof(uint32_t) * ((size_t)nitems + 1);
     if (lds < need) lds = need;
-    return launch_kernel(batched_queue_kernel<T, Op, kQSub>, dim3(grid), dim3(kB), lds, s,
+    return launch_kernel(batched_queue_kernel<T, Op>, dim3(grid), dim3(kB), lds, s,
                          d_items, nitems, q);
 }
 
@@ -1003,7 +702,7 @@ constexpr size_t rr_lds_bytes(int nitems)
 constexpr size_t kRrLdsStep = 4096;
 constexpr int kRrLdsSteps = (int)((rr_lds_bytes(kRrMaxItems) + kRrLdsStep - 1) / kRrLdsStep);
 
-template <class T, class Op, bool PLANNED>
+template <class T, class Op>
 int rr_per_cu(int steps)
 {
     static int cache[kMaxDevicesCached][kRrLdsSteps + 1];
@@ -1011,8 +710,8 @@ int rr_per_cu(int steps)
     int v = __atomic_load_n(&cache[dev][steps], __ATOMIC_RELAXED);
     if (v <= 0) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &v, (const void *)batched_rr_kernel<T, Op, PLANNED>, kB,
-                (size_t)steps * kRrLdsStep) != hipSuccess ||
+                &v, (const void *)batched_rr_kernel<T, Op>, kB, (size_t)steps * kRrLdsStep) !=
+                hipSuccess ||
             v <= 0)
             v = 1;
         __atomic_store_n(&cache[dev][steps], v, __ATOMIC_RELAXED);
@@ -1021,18 +720,12 @@ int rr_per_cu(int steps)
 }
 
 template <class T, class Op>
-hipError_t go_rr(bool planned, const xred_item *d_items, int nitems, const uint32_t *d_tile_start,
-                 hipStream_t s)
+hipError_t go_rr(const xred_item *d_items, int nitems, const uint32_t *d_tile_start, hipStream_t s)
 {
     const int steps = (int)((rr_lds_bytes(nitems) + kRrLdsStep - 1) / kRrLdsStep);
-    const size_t lds = (size_t)steps * kRrLdsStep;
-    const int per_cu = planned ? rr_per_cu<T, Op, true>(steps) : rr_per_cu<T, Op, false>(steps);
-    const unsigned grid = batched_rr_grid(per_cu);
-    if (planned)
-        return launch_kernel(batched_rr_kernel<T, Op, true>, dim3(grid), dim3(kB), lds, s,
-                             d_items, nitems, d_tile_start);
-    return launch_kernel(batched_rr_kernel<T, Op, false>, dim3(grid), dim3(kB), lds, s, d_items,
-                         nitems, d_tile_start);
+    const unsigned grid = batched_rr_grid(rr_per_cu<T, Op>(steps));
+    return launch_kernel(batched_rr_kernel<T, Op>, dim3(grid), dim3(kB),
+                         (size_t)steps * kRrLdsStep, s, d_items, nitems, d_tile_start);
 }
 
 template <class T, class Op>
@@ -1060,11 +753,10 @@ template <class... Ts>
 hipError_t batched_rr_group(xred_dtype dtype, xred_op op, const xred_item *d_items, int nitems,
                             const uint32_t *d_tile_start, hipStream_t s)
 {
-    const bool planned = d_tile_start != nullptr;
     return with_dtype_among<Ts...>(dtype, [&](auto t) {
         using T = decltype(t);
         return with_op<T, true>(op, [&](auto o) {
-            return go_rr<T, decltype(o)>(planned, d_items, nitems, d_tile_start, s);
+            return go_rr<T, decltype(o)>(d_items, nitems, d_tile_start, s);
         });
     });
 }

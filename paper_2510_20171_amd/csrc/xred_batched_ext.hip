@@ -23,12 +23,11 @@ hipError_t launch_batched_table_ext(xred_dtype dtype, xred_op op, const xred_ite
                                                   ntiles, stream);
 }
 
-hipError_t launch_batched_grouped_ext(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                 int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                 int wgs_per_cu, hipStream_t stream)
+hipError_t launch_batched_runs_ext(xred_dtype dtype, xred_op op, const xred_item *d_items,
+                              int nitems, uint32_t nruns, uint32_t m, unsigned grid,
+                              hipStream_t stream)
 {
-    return batched_grouped_group<TF64, TI8, TU8>(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+    return batched_runs_group<TF64, TI8, TU8>(dtype, op, d_items, nitems, nruns, m, grid, stream);
 }
 
 hipError_t launch_batched_queue_ext(xred_dtype dtype, xred_op op, const xred_item *d_items,

@@ -23,12 +23,11 @@ hipError_t launch_batched_table_float(xred_dtype dtype, xred_op op, const xred_i
                                                   ntiles, stream);
 }
 
-hipError_t launch_batched_grouped_float(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                 int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                 int wgs_per_cu, hipStream_t stream)
+hipError_t launch_batched_runs_float(xred_dtype dtype, xred_op op, const xred_item *d_items,
+                              int nitems, uint32_t nruns, uint32_t m, unsigned grid,
+                              hipStream_t stream)
 {
-    return batched_grouped_group<TF32, TBF16, TF16>(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+    return batched_runs_group<TF32, TBF16, TF16>(dtype, op, d_items, nitems, nruns, m, grid, stream);
 }
 
 hipError_t launch_batched_queue_float(xred_dtype dtype, xred_op op, const xred_item *d_items,

@@ -23,12 +23,11 @@ hipError_t launch_batched_table_int(xred_dtype dtype, xred_op op, const xred_ite
                                                   ntiles, stream);
 }
 
-hipError_t launch_batched_grouped_int(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                 int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                 int wgs_per_cu, hipStream_t stream)
+hipError_t launch_batched_runs_int(xred_dtype dtype, xred_op op, const xred_item *d_items,
+                              int nitems, uint32_t nruns, uint32_t m, unsigned grid,
+                              hipStream_t stream)
 {
-    return batched_grouped_group<TI32, TU32, TI64, TU64>(dtype, op, d_items, nitems, ngroups, m, grid,
-                                          wgs_per_cu, stream);
+    return batched_runs_group<TI32, TU32, TI64, TU64>(dtype, op, d_items, nitems, nruns, m, grid, stream);
 }
 
 hipError_t launch_batched_queue_int(xred_dtype dtype, xred_op op, const xred_item *d_items,

@@ -115,24 +115,20 @@ hipError_t launch_batched_planned(xred_dtype dtype, xred_op op, const xred_item 
 // Grid of the host-planned range layout.
 unsigned batched_device_grid();
 
-// Round-robin batched kernel (batches of at most batched_rr_max_items()
-// items).  d_tile_start: the host plan (nitems + 1 exclusive tile-start
-// prefix values), or NULL to have every workgroup compute it from the
-// device-resident descriptors.
+// Round-robin batched kernel (host batches of at most batched_rr_max_items()
+// items).  d_tile_start: the host plan, nitems + 1 exclusive tile-start
+// prefix values.
 int batched_rr_max_items();
 hipError_t launch_batched_rr(xred_dtype dtype, xred_op op, const xred_item *d_items, int nitems,
                              const uint32_t *d_tile_start, hipStream_t stream);
 
-// Device-resident descriptors, grouped: the batch is cut into ngroups runs of
-// at most batched_grouped_max_items() consecutive items, each run is dealt to
-// m workgroups tile by tile, and grid (a multiple of m, at least m) is
-// m * ngroups or fewer under a CU budget.  wgs_per_cu: workgroups allowed to
-// share one CU (the kernel's LDS reservation enforces it; m should be the
-// device's CUs times it).
-int batched_grouped_max_items();
-hipError_t launch_batched_grouped(xred_dtype dtype, xred_op op, const xred_item *d_items,
-                                  int nitems, uint32_t ngroups, uint32_t m, unsigned grid,
-                                  int wgs_per_cu, hipStream_t stream);
+// Device-resident descriptors without state: the batch is cut into nruns runs
+// of batched_run_items() consecutive items (the last one shorter), each run
+// is dealt to m workgroups tile by tile, and grid (a multiple of m, at least
+// m) is m * nruns or fewer under a CU budget.
+int batched_run_items();
+hipError_t launch_batched_runs(xred_dtype dtype, xred_op op, const xred_item *d_items, int nitems,
+                               uint32_t nruns, uint32_t m, unsigned grid, hipStream_t stream);
 
 // The batched launchers per group of element types (each in its own
 // translation unit).
@@ -145,10 +141,9 @@ hipError_t launch_batched_grouped(xred_dtype dtype, xred_op op, const xred_item 
     hipError_t launch_batched_table_##G(xred_dtype dtype, xred_op op, const xred_item *d_items, \
                                         const uint32_t *d_table, bool narrow, uint64_t ntiles, \
                                         hipStream_t s);                                        \
-    hipError_t launch_batched_grouped_##G(xred_dtype dtype, xred_op op,                        \
-                                          const xred_item *d_items, int nitems,                \
-                                          uint32_t ngroups, uint32_t m, unsigned grid,         \
-                                          int wgs_per_cu, hipStream_t s);                      \
+    hipError_t launch_batched_runs_##G(xred_dtype dtype, xred_op op, const xred_item *d_items, \
+                                       int nitems, uint32_t nruns, uint32_t m, unsigned grid,  \
+                                       hipStream_t s);                                         \
     hipError_t launch_batched_queue_##G(xred_dtype dtype, xred_op op,                          \
                                         const xred_item *d_items, int nitems, uint64_t *next,  \
                                         uint64_t *clear, uint64_t *finished, unsigned grid,    \
