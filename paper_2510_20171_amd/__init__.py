@@ -1,7 +1,8 @@
 """libxred: one rank's reduce step of ReduceScatter / AllReduce on MI355X.
 
 Thin Python binding over the C ABI in include/xred.h (argument marshalling
-only; every step runs in the HIP kernels of libxred.so).  PyTorch supplies
+only, compiled for plain tensors; every step runs in the HIP kernels of
+libxred.so).  PyTorch supplies
 device memory and streams: tensors are passed as data pointers and the
 current HIP stream of the tensor's device is used unless one is given.
 
@@ -23,7 +24,7 @@ import ctypes
 from ._lib import (ACC_SIZE, ALIAS, DTYPE, ELEM_SIZE, EXPORTS, HIP_ERROR, INVALID_ARGUMENT,
                    ITEM_DTYPE,
                    ITEMS_ON_DEVICE, MAX_SRC, OP, OUT_OF_MEMORY, SCHEDULE, STEP_FINAL, STEP_INIT,
-                   SUCCESS, UNSUPPORTED, XredError, XredItem, check, load, ptr_array)
+                   SUCCESS, UNSUPPORTED, XredError, XredItem, check, load, native, ptr_array)
 
 __all__ = ["allreduce_local", "reduce_scatter_local", "reduce_copy_step", "acc_cast",
            "batched_reduce_noalloc",
@@ -85,7 +86,7 @@ def _stream(t, stream):
     if stream is not None:
         return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.device.index))
 
 
 def _ptr(t):
@@ -94,6 +95,9 @@ def _ptr(t):
 
 def allreduce_local(srcs, out, op: str = "sum", *, dtype=None, stream=None) -> None:
     """out[i] = fold_op(srcs[0][i], ..., srcs[P-1][i]) in source order (xred_allreduce_local)."""
+    st = native().allreduce(srcs, out, op, dtype, stream)
+    if st is not None:   # plain tensors; anything else is checked below
+        return check(st)
     L = load()
     n = out.numel()
     dt = _dtype_name(out, dtype)
@@ -106,6 +110,9 @@ def allreduce_local(srcs, out, op: str = "sum", *, dtype=None, stream=None) -> N
 def reduce_scatter_local(srcs, rank: int, out, op: str = "sum", *, dtype=None,
                          stream=None) -> None:
     """Shard `rank` of a ReduceScatter over full send buffers srcs (xred_reduce_scatter_local)."""
+    st = native().scatter(srcs, rank, out, op, dtype, stream)
+    if st is not None:
+        return check(st)
     L = load()
     dt = _dtype_name(out, dtype)
     _require([out], out.numel(), ELEM_SIZE[dt], "out", out.device)
@@ -118,8 +125,11 @@ def reduce_scatter_local(srcs, rank: int, out, op: str = "sum", *, dtype=None,
 def reduce_copy_step(inp, acc, out=None, op: str = "sum", *, init: bool = False,
                      final: bool = False, dtype=None, stream=None) -> None:
     """One ring ReduceCopy step into a 4-byte accumulator (xred_reduce_copy_step)."""
-    L = load()
     flags = (STEP_INIT if init else 0) | (STEP_FINAL if final else 0)
+    st = native().step(inp, acc, out, op, flags, dtype, stream)
+    if st is not None:
+        return check(st)
+    L = load()
     n = inp.numel()
     dt = _dtype_name(inp, dtype)
     _require([inp], n, ELEM_SIZE[dt], "in", inp.device)
@@ -137,6 +147,9 @@ def reduce_copy_step(inp, acc, out=None, op: str = "sum", *, init: bool = False,
 
 def acc_cast(acc, out, *, dtype=None, stream=None) -> None:
     """out = down(acc): closing cast of a step-wise sequence (xred_acc_cast)."""
+    st = native().cast(acc, out, dtype, stream)
+    if st is not None:
+        return check(st)
     L = load()
     dt = _dtype_name(out, dtype)
     _require([out], out.numel(), ELEM_SIZE[dt], "out", out.device)
@@ -172,6 +185,9 @@ def batched_reduce(items, op: str = "sum", *, dtype: str, stream=None, device=No
         st = _stream(items, stream)
         check(L.xred_batched_reduce(_ptr(items), n, DTYPE[dtype], OP[op], ITEMS_ON_DEVICE, st))
         return
+    st = native().batched(items, op, dtype, stream)
+    if st is not None:
+        return check(st)
     keep = []
     rows = []
     es = ELEM_SIZE[_dtype_name(None, dtype)]
@@ -209,6 +225,9 @@ def ring_reduce(chunks, out, op: str = "sum", *, ready=None, epoch: int = 1,
     ready: None, or a tensor of len(chunks) uint32/int32 flags in pinned host
     or device memory; status: None or a 1-element int32 tensor (pinned or
     device) that receives 1 if a wait timed out."""
+    st = native().ring(chunks, out, op, ready, epoch, timeout_us, status, dtype, stream)
+    if st is not None:
+        return check(st)
     L = load()
     dt = _dtype_name(out, dtype)
     _require([out], out.numel(), ELEM_SIZE[dt], "out", out.device)
@@ -226,6 +245,9 @@ def allreduce_sim(sends, recvs, op: str = "sum", *, schedule: str = "ring", dtyp
     (xred_allreduce_sim): recvs[r] receives the reduced buffer at every rank.
     schedule: "ring" or "rhd" (recursive halving-doubling), one launch per step, or
     "ring1" / "rhd1", every step in one launch (same bits)."""
+    st = native().sim(sends, recvs, op, schedule, dtype, stream)
+    if st is not None:
+        return check(st)
     L = load()
     if len(sends) != len(recvs):
         raise XredError(INVALID_ARGUMENT, "one recv buffer per send buffer")

@@ -12,6 +12,7 @@ from pathlib import Path
 import numpy as np
 
 LIB_PATH = Path(__file__).resolve().parent / "libxred.so"
+NATIVE_PATH = LIB_PATH.with_name("_xred_torch.so")   # the binding's tensor marshalling
 
 # Values of the enums in include/xred.h.
 DTYPE = {"f32": 0, "bf16": 1, "f16": 2, "i32": 3, "u32": 4, "i64": 5, "u64": 6, "e4m3": 7,
@@ -48,6 +49,7 @@ EXPORTS = ("xred_allreduce_local", "xred_reduce_scatter_local", "xred_reduce_cop
            "xred_last_error", "xred_version", "xred_release")
 
 _lib = None
+_native = None
 
 
 class XredError(RuntimeError):
@@ -109,6 +111,27 @@ def load(path: Path = LIB_PATH) -> ctypes.CDLL:
     L.xred_release.restype = None
     _lib = L
     return L
+
+
+def native():
+    """The compiled marshalling module (csrc/xred_torch.cpp), bound to libxred.so."""
+    global _native
+    if _native is not None:
+        return _native
+    L = load()
+    if not NATIVE_PATH.exists():
+        raise ImportError(f"{NATIVE_PATH} is not built: run "
+                          "`python -m paper_2510_20171_amd.build`")
+    import importlib.util
+
+    import torch
+    spec = importlib.util.spec_from_file_location("_xred_torch", NATIVE_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.bind(torch._C._cuda_getCurrentRawStream,
+             {f: ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in EXPORTS})
+    _native = mod
+    return mod
 
 
 def check(status: int) -> None:

@@ -4,7 +4,9 @@
 
 Every .hip file under csrc/ is compiled to an object in parallel, then linked
 into paper_2510_20171_amd/libxred.so; ceiling/xred_ceiling.hip (a measuring
-tool for bench.py) becomes paper_2510_20171_amd/libxred_ceiling.so.  Flags:
+tool for bench.py) becomes paper_2510_20171_amd/libxred_ceiling.so, and
+csrc/xred_torch.cpp (host code, the host compiler) the Python module
+_xred_torch.so the binding marshals tensors with.  Flags of the HIP code:
   --offload-arch=gfx950      MI355X only
   -ffp-contract=off          no fused multiply-add: one IEEE op per float op
   -fno-gpu-flush-denormals-to-zero   binary32 subnormals are kept
@@ -31,6 +33,9 @@ OUT = PKG / "libxred.so"
 # library: not part of libxred's interface)
 CEILING_SRC = PKG / "ceiling" / "xred_ceiling.hip"
 CEILING_OUT = PKG / "libxred_ceiling.so"
+# the binding's tensor marshalling (a CPython module against torch's headers)
+TORCH_SRC = CSRC / "xred_torch.cpp"
+TORCH_OUT = PKG / "_xred_torch.so"
 BUILD = PKG / "_build"
 HIPCC = "/opt/rocm/bin/hipcc"
 
@@ -54,6 +59,19 @@ def _run(cmd):
         print(err, file=sys.stderr)
 
 
+def _torch_module_cmd(out: Path):
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    incs = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    lib = Path(torch.__file__).resolve().parent / "lib"
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *(x for i in incs for x in ("-isystem", i)), str(TORCH_SRC), "-o", str(out),
+            f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{lib}"]
+
+
 def build(jobs: int = 0, verbose: bool = False) -> Path:
     """Compile every csrc/*.hip and link libxred.so; returns its path."""
     BUILD.mkdir(exist_ok=True)
@@ -62,6 +80,8 @@ def build(jobs: int = 0, verbose: bool = False) -> Path:
     cmds = [[HIPCC, *HIPFLAGS, "-c", str(s), "-o", str(o)] for s, o in zip(sources, objs)]
     ceiling_tmp = CEILING_OUT.with_suffix(".so.tmp")
     cmds.append([HIPCC, *HIPFLAGS, "-shared", str(CEILING_SRC), "-o", str(ceiling_tmp)])
+    torch_tmp = TORCH_OUT.with_suffix(".so.tmp")
+    cmds.append(_torch_module_cmd(torch_tmp))
     if jobs <= 0:
         jobs = min(16, os.cpu_count() or 4)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -70,8 +90,9 @@ def build(jobs: int = 0, verbose: bool = False) -> Path:
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)])
     tmp.replace(OUT)
     ceiling_tmp.replace(CEILING_OUT)
+    torch_tmp.replace(TORCH_OUT)
     if verbose:
-        print(f"built {OUT} and {CEILING_OUT}")
+        print(f"built {OUT}, {TORCH_OUT} and {CEILING_OUT}")
     return OUT
 
 
