@@ -505,7 +505,7 @@ def secondary(torch, xr, L, timer, wl, flush, res):
     # reduce-scatter over the same share (P=8 bf16, 8 ranks, shards of 2^23
     # and 2^23 + 1 elements): with the odd length rank 1's shard starts 2
     # bytes past a 16-byte boundary in every send buffer while its output is
-    # aligned (the realigned stores); rank 0's is aligned either way
+    # aligned (unaligned stores); rank 0's is aligned either way
     rs = {}
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     for rc in (1 << 23, (1 << 23) + 1):
