@@ -481,19 +481,19 @@ __device__ __forceinline__ size_t xcd_run_tile(size_t i, size_t ntiles)
 // pointer at the same offset within 16 bytes: the first `lead` elements
 // (fewer than a vector) bring them all to a 16-byte boundary and, like the
 // last `tail` ones, are done by one workgroup, scalar; the nvec vectors
-// between go in tiles of B vectors (the last one ragged, cut by the buffer
+// between go in tiles of B * U vectors (the last one ragged, cut by the buffer
 // range check).  `head` (a multiple of 16 below 128, at most nvec*16) is the
 // byte length of a first, short tile that ends where the first source
 // reaches a 128-byte line: the other tiles then start on line boundaries, so
 // no line is split between two tiles (whose workgroups, on different XCDs,
 // would each fetch it).
 // runs: tiles in runs of 32 per XCD (xcd_run_tile), else in address order.
-template <class T, class Op, int NP, int MAXP, int B>
+template <class T, class Op, int NP, int MAXP, int U, int B>
 __global__ __launch_bounds__(B) void reduce_vec_kernel(KernargSrc<MAXP> src, int nsrc, char *dst,
                                                        size_t nvec, uint32_t tail, uint32_t head,
                                                        uint32_t lead, bool runs)
 {
-    constexpr uint32_t kTileBytes = (uint32_t)B * 16u;
+    constexpr uint32_t kTileBytes = (uint32_t)B * U * 16u;
     const size_t vbytes = nvec * 16;
     const size_t lb = (size_t)lead * T::kSize;   // bytes before the first vector
     const uint32_t first = head != 0 ? 1u : 0u;
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(B) void reduce_vec_kernel(KernargSrc<MAXP> src, int
         const size_t t = runs ? xcd_run_tile(i, ntiles) : i;
         const bool h = t < first;
         const size_t off = h ? 0 : head + (t - first) * kTileBytes;
-        reduce_tile<T, Op, NP, 1, B>(src, nsrc, dst,
+        reduce_tile<T, Op, NP, U, B>(src, nsrc, dst,
                                      Tile{lb + off, h ? head : tile_nrec(vbytes, off, kTileBytes)});
     }
     if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)

@@ -15,16 +15,24 @@
 namespace xred {
 namespace {
 
-// Two tile shapes, one 16-byte vector of every source per thread:
+// Three tile shapes, one 16-byte vector of every source per thread but for the second:
 //
 // * Up to 8 sources, launches that fit on the chip in one round (every tile
 //   resident at once: up to 8 MiB per source) are latency-bound: 512-thread
 //   workgroups, uncapped, so the whole message is in flight after the fewest
 //   workgroup dispatches (P=8 bf16 4 MiB per source 6.8 us against 7.0-7.4
-//   with 128 threads; equal at 7 MiB).  More sources are bound by what a
-//   CU keeps in flight, so they spread over the chip in 128-thread
-//   workgroups at any size (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us
-//   against 8.1 / 23.6 / 41.6).
+//   with 128 threads; equal at 7 MiB).  More sources spread over the chip in
+//   128-thread workgroups (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us against
+//   8.1 / 23.6 / 41.6; P=16 512 KiB 3.1 against 4.3), except in the next case.
+// * A call of at most 128 MiB of sources and output (half the MALL) mostly finds
+//   the last step's buffers there, and is then bound by dispatches and by what
+//   the wave cap keeps out rather than by HBM.  While they fit in one round, up to
+//   8 sources take 512-thread workgroups of two vectors a thread, and more
+//   sources past 1 MiB each those of one, uncapped (bf16, this / 128-thread tiles:
+//   P=2 12 MiB 4.3 / 6.8 us, P=4 9 / 16 MiB 7.3 / 8.2, 11.2 / 13.5, P=8 12 MiB
+//   15.6 / 18.3; P=9 4 MiB 5.8 / 9.2, P=16 2 / 4 MiB 5.2 / 5.4, 9.6 / 11.2).  Above
+//   it the 128-thread tiles win where the data comes from HBM (P=8 16 MiB 25.2 /
+//   23.5).
 // * Larger launches are bandwidth-bound: 128-thread workgroups with a
 //   bounded number of waves per CU.  HBM3E on MI355X delivers the most when
 //   a CU keeps a moderate number of loads in flight; more waves than that
@@ -57,9 +65,13 @@ namespace {
 constexpr int kB = 128;        // threads per workgroup, bandwidth-bound launches
 constexpr int kBWide = 512;    // threads per workgroup, one-round launches
 constexpr int kWideWgsPerCu = 4;   // resident 512-thread workgroups per CU
+constexpr size_t kCachedBytes = (size_t)128 << 20;   // sources and output of a MALL-sized call
 
+// One source stays in address order: a copy that fits the L2s is served from
+// them when an XCD meets its last call's lines (20 MiB 5.2 us, in runs 7.1).
 bool run_order(const char *const *srcs, int nsrc, const char *dst, size_t bytes)
 {
+    if (nsrc == 1) return false;
     if ((size_t)nsrc * bytes <= ((size_t)512 << 20)) return true;
     uintptr_t any = (uintptr_t)dst, diff = 0;
     for (int p = 0; p < nsrc; ++p) {
@@ -197,16 +209,24 @@ hipError_t go_vec(const char *const *srcs, int nsrc, char *dst, size_t count, ui
     const uint32_t head = (uint32_t)(mis == 0 ? 0 : std::min<size_t>(128 - mis, nvec * 16));
     const size_t hv = head / 16, first = head != 0 ? 1 : 0;
     const uint64_t extra = (tail | lead) ? 1 : 0;
-    if constexpr (NP >= 1 && NP <= 8) {
-        const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
-        if (tiles_wide <= (uint64_t)device_cus() * kWideWgsPerCu)
-            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kBWide>,
-                                 dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst,
+    const size_t bytes = count * T::kSize;
+    const bool cached = bytes <= kCachedBytes / ((size_t)nsrc + 1);
+    constexpr bool kFew = NP >= 1 && NP <= 8;
+    const uint64_t one_round = (uint64_t)device_cus() * kWideWgsPerCu;
+    const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
+    if (tiles_wide <= one_round && (kFew || (cached && bytes > ((size_t)1 << 20))))
+        return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kBWide>,
+                             dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst, nvec,
+                             tail, head, lead, false);
+    if constexpr (kFew) {
+        const uint64_t tiles_wide2 = first + (nvec - hv + 2 * kBWide - 1) / (2 * kBWide) + extra;
+        if (tiles_wide2 <= one_round && cached)
+            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 2, kBWide>,
+                                 dim3(grid_for(tiles_wide2)), dim3(kBWide), 0, s, ks, nsrc, dst,
                                  nvec, tail, head, lead, false);
     }
     const uint64_t tiles = first + (nvec - hv + kB - 1) / kB + extra;
-    const size_t bytes = count * T::kSize;
-    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, kB>, dim3(grid_for(tiles)), dim3(kB),
+    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kB>, dim3(grid_for(tiles)), dim3(kB),
                          lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst, nvec,
                          tail, head, lead, run_order(srcs, nsrc, dst, bytes));
 }

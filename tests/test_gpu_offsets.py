@@ -75,3 +75,14 @@ def test_offsets_xcd_runs(xr, orc, dtype, extra):
             _run(xr, orc, dtype, "sum", 3, n, [1, 0, 3], 2, n)
         finally:
             xr.set_max_workgroups(prev)
+
+
+@pytest.mark.parametrize("P,nbytes", [(8, (128 << 20) // 9), (8, 9 << 20), (2, 16 << 20),
+                                      (9, 1 << 20), (16, (128 << 20) // 17), (1, 17 << 20)])
+def test_cached_shapes(xr, orc, P, nbytes):
+    """Sizes at the edges of the shapes for calls of at most 128 MiB (one and
+    two vectors per thread, more than 8 sources past 1 MiB), on and off the
+    sources' grid."""
+    for n in (nbytes // 16 * 8, nbytes // 16 * 8 + 9):
+        for src, dst in ((0, 0), (1, 0)):
+            _run(xr, orc, "bf16", "sum", P, n, [src] * P, dst, n)
