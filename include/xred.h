@@ -239,12 +239,15 @@ XRED_API xred_status xred_acc_cast(const void *acc, void *dst, size_t count, xre
  *            read when the kernels run, so an earlier kernel on the stream may
  *            still write them (metadata by reference, after the GPU-resident
  *            collectives of Section 6.1).  No host work per item: the kernel
- *            plans the batch from the descriptors.  Batches of up to 16384
+ *            plans the batch from the descriptors.  Batches of 65..16384
  *            items launched eagerly take tiles in order from a counter pair
  *            in device memory the library binds to the calling stream (64
- *            streams per device, allocated once, until xred_release);
- *            under graph capture, past 64 streams or past 16384 items the
- *            batch runs on a kernel that keeps no state, so the call can be
+ *            streams per device, allocated once, until xred_release; the
+ *            first such call on a device allocates them and waits for its
+ *            stream, so it must not fall into another thread's global-mode
+ *            capture); batches of up to 64 items, and all under graph
+ *            capture, past 64 streams or past 16384 items, run on a kernel
+ *            that keeps no state and allocates nothing, so the call can be
  *            captured in a HIP graph (same results).  Items that cannot be
  *            run safely (nsrc outside 1..64, a NULL pointer, reserved != 0)
  *            are skipped and their dst is left untouched; pointers are

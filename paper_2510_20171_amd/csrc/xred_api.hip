@@ -609,10 +609,17 @@ unsigned batched_device_grid()
     return grid_for((uint64_t)device_cus() * (uint64_t)per_cu);
 }
 
-// Device-resident descriptors: the queue kernel, or under graph capture (a
-// replay would repeat the captured counter), past the queue's item limit, or
-// without a slot, the stateless runs kernel.  Under a CU budget the latter
-// takes fewer workgroups per run and fewer runs at a time.
+// Device-resident descriptors: the queue kernel for more items than one run
+// holds, up to its item limit; the stateless runs kernel for other batches,
+// under graph capture (a replay would repeat the captured counter), or without
+// a slot.  Under a CU budget the latter takes fewer workgroups per run and
+// fewer runs at a time.
+//
+// A batch of one run binds no slot: the first launch that does allocates and
+// waits for its stream, and a slot follows a stream's handle.  It is the
+// faster one too until the items are large (bf16 log-uniform to 1 MiB, runs /
+// queue: 16 items of P=2 6.6 / 8.4 us, 32 of P=8 13.1 / 16.6, 48 of P=4 9.1 /
+// 13.3, 64 of P=8 24.2 / 26.4; 64 of 1 MiB 105.7 / 100.8, 64 of 8 MiB 857 / 760).
 hipError_t batched_device(const xred_item *items, int nitems, xred_dtype dtype, xred_op op,
                           hipStream_t stream)
 {
@@ -620,7 +627,7 @@ hipError_t batched_device(const xred_item *items, int nitems, xred_dtype dtype, 
     // launch takes tiles from counter (launches % 2), zeroed by the launch
     // before it on the stream (or when the slot was created), and zeroes the
     // other one for the launch after it.
-    if (nitems <= batched_queue_max_items()) {
+    if (nitems > batched_run_items() && nitems <= batched_queue_max_items()) {
         StreamSlot slot;
         if (slot.acquire(kSlotQueue, stream)) {
             uint64_t *c = (uint64_t *)slot.words;
