@@ -7,12 +7,13 @@ kernels.
 from __future__ import annotations
 
 import ctypes
+import logging
 from pathlib import Path
 
 import numpy as np
 
 LIB_PATH = Path(__file__).resolve().parent / "libxred.so"
-NATIVE_PATH = LIB_PATH.with_name("_xred_torch.so")   # the binding's tensor marshalling
+NATIVE_PATH = LIB_PATH.with_name("_xred_torch.so")   # the binding's marshalling, optional
 
 # Values of the enums in include/xred.h.
 DTYPE = {"f32": 0, "bf16": 1, "f16": 2, "i32": 3, "u32": 4, "i64": 5, "u64": 6, "e4m3": 7,
@@ -113,25 +114,47 @@ def load(path: Path = LIB_PATH) -> ctypes.CDLL:
     return L
 
 
-def native():
-    """The compiled marshalling module (csrc/xred_torch.cpp), bound to libxred.so."""
+class _Declines:
+    """Stands in for the marshalling module: leaves every call to the Python code."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(L, path: Path):
+    import importlib.util
+    import sys
+
+    import torch
+    if not path.exists():
+        raise ImportError(f"{path} is not built")
+    spec = importlib.util.spec_from_file_location("_xred_torch", path)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    python = f"{sys.version_info[0]}.{sys.version_info[1]}"
+    if mod.python != python or not torch.__version__.startswith(mod.torch):
+        raise ImportError(f"{path} is built for Python {mod.python} and torch {mod.torch}, "
+                          f"not {python} and {torch.__version__}")
+    mod.bind(torch._C._cuda_getCurrentRawStream,
+             {f: ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in EXPORTS})
+    return mod
+
+
+def native(path: Path = NATIVE_PATH):
+    """The compiled marshalling module (csrc/xred_torch.cpp), loaded once and
+    bound to libxred.so.  It only makes calls cheaper: where it is missing, or
+    built for another Python or torch, the binding's Python code makes the same
+    calls of the same library."""
     global _native
     if _native is not None:
         return _native
     L = load()
-    if not NATIVE_PATH.exists():
-        raise ImportError(f"{NATIVE_PATH} is not built: run "
-                          "`python -m paper_2510_20171_amd.build`")
-    import importlib.util
-
-    import torch
-    spec = importlib.util.spec_from_file_location("_xred_torch", NATIVE_PATH)
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
-    mod.bind(torch._C._cuda_getCurrentRawStream,
-             {f: ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in EXPORTS})
-    _native = mod
-    return mod
+    try:
+        _native = _load_native(L, Path(path))
+    except ImportError as e:
+        logging.getLogger(__name__).warning("calls are marshalled in Python: %s", e)
+        _native = _Declines()
+    return _native
 
 
 def check(status: int) -> None:

@@ -6,7 +6,9 @@ Every .hip file under csrc/ is compiled to an object in parallel, then linked
 into paper_2510_20171_amd/libxred.so; ceiling/xred_ceiling.hip (a measuring
 tool for bench.py) becomes paper_2510_20171_amd/libxred_ceiling.so, and
 csrc/xred_torch.cpp (host code, the host compiler) the Python module
-_xred_torch.so the binding marshals tensors with.  Flags of the HIP code:
+_xred_torch.so the binding marshals tensors with.  That module is left out,
+with a note, where g++, Python.h or torch's headers are missing: the library
+needs none of them.  Flags of the HIP code:
   --offload-arch=gfx950      MI355X only
   -ffp-contract=off          no fused multiply-add: one IEEE op per float op
   -fno-gpu-flush-denormals-to-zero   binary32 subnormals are kept
@@ -21,6 +23,7 @@ _xred_torch.so the binding marshals tensors with.  Flags of the HIP code:
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -60,13 +63,20 @@ def _run(cmd):
 
 
 def _torch_module_cmd(out: Path):
+    """The command that builds the marshalling module; ImportError names what is missing."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
+    gxx = shutil.which("g++")
+    if gxx is None:
+        raise ImportError("g++ is missing")
     incs = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    for header in ("Python.h", "torch/csrc/autograd/python_variable.h"):
+        if not any((Path(i) / header).exists() for i in incs):
+            raise ImportError(f"{header} is missing")
     lib = Path(torch.__file__).resolve().parent / "lib"
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+    return [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             *(x for i in incs for x in ("-isystem", i)), str(TORCH_SRC), "-o", str(out),
             f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{lib}"]
@@ -81,7 +91,13 @@ def build(jobs: int = 0, verbose: bool = False) -> Path:
     ceiling_tmp = CEILING_OUT.with_suffix(".so.tmp")
     cmds.append([HIPCC, *HIPFLAGS, "-shared", str(CEILING_SRC), "-o", str(ceiling_tmp)])
     torch_tmp = TORCH_OUT.with_suffix(".so.tmp")
-    cmds.append(_torch_module_cmd(torch_tmp))
+    try:
+        cmds.append(_torch_module_cmd(torch_tmp))
+    except ImportError as e:
+        print(f"{TORCH_OUT.name} is not built ({e}): calls will be marshalled in Python",
+              file=sys.stderr)
+        TORCH_OUT.unlink(missing_ok=True)
+        torch_tmp = None
     if jobs <= 0:
         jobs = min(16, os.cpu_count() or 4)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -90,9 +106,10 @@ def build(jobs: int = 0, verbose: bool = False) -> Path:
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)])
     tmp.replace(OUT)
     ceiling_tmp.replace(CEILING_OUT)
-    torch_tmp.replace(TORCH_OUT)
+    if torch_tmp is not None:
+        torch_tmp.replace(TORCH_OUT)
     if verbose:
-        print(f"built {OUT}, {TORCH_OUT} and {CEILING_OUT}")
+        print(f"built {OUT}{f', {TORCH_OUT}' if torch_tmp else ''} and {CEILING_OUT}")
     return OUT
 
 

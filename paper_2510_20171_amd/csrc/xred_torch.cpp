@@ -13,6 +13,7 @@
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstring>
 #include <exception>
@@ -386,4 +387,21 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_xred_torch",
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__xred_torch() { return PyModule_Create(&module); }
+#define XRED_TEXT_(x) #x
+#define XRED_TEXT(x) XRED_TEXT_(x)
+
+// `python` and `torch`: what the module was compiled against, for the loader.
+PyMODINIT_FUNC PyInit__xred_torch()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr &&
+        (PyModule_AddStringConstant(
+             m, "python", XRED_TEXT(PY_MAJOR_VERSION) "." XRED_TEXT(PY_MINOR_VERSION)) < 0 ||
+         PyModule_AddStringConstant(m, "torch",
+                                    XRED_TEXT(TORCH_VERSION_MAJOR) "." XRED_TEXT(
+                                        TORCH_VERSION_MINOR) "." XRED_TEXT(TORCH_VERSION_PATCH)) < 0)) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

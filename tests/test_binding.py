@@ -113,3 +113,53 @@ def test_library_shares_torchs_hip_runtime():
                          timeout=300, check=True).stdout
     runtimes = ast.literal_eval(out.strip().splitlines()[-1])
     assert len(runtimes) == 1, runtimes
+
+
+def _calls_go_to_python():
+    out = FakeGpuTensor(100)
+    _invalid(lambda: xr.allreduce_local([FakeGpuTensor(100), FakeGpuTensor(99)], out),
+             "srcs[1] has 99 elements")
+
+
+def test_binding_without_the_compiled_module(monkeypatch, tmp_path, caplog):
+    """The marshalling module only makes calls cheaper: missing, not loadable,
+    or built for another torch, the Python code takes every call."""
+    from paper_2510_20171_amd import _lib
+    broken = tmp_path / "_xred_torch.so"
+    broken.write_bytes(b"not a shared object")
+    for path in (tmp_path / "missing.so", broken):
+        monkeypatch.setattr(_lib, "_native", None)
+        assert _lib.native(path).allreduce([], None, "sum", None, None) is None
+        assert "marshalled in Python" in caplog.text
+        _calls_go_to_python()
+    if _lib.NATIVE_PATH.exists():
+        monkeypatch.setattr(_lib, "_native", None)
+        monkeypatch.setattr(torch, "__version__", "1.0.0")
+        assert isinstance(_lib.native(), _lib._Declines)
+        assert "not 3." in caplog.text and "1.0.0" in caplog.text
+        _calls_go_to_python()
+
+
+def test_build_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    """Without g++ (or the headers) the library is built all the same, and no
+    marshalling module of an earlier build is left beside it."""
+    import shutil
+    from pathlib import Path
+
+    from paper_2510_20171_amd import build
+    for name in ("OUT", "CEILING_OUT", "TORCH_OUT"):
+        monkeypatch.setattr(build, name, tmp_path / getattr(build, name).name)
+    monkeypatch.setattr(build, "BUILD", tmp_path / "objects")
+    build.TORCH_OUT.write_bytes(b"stale")
+    commands = []
+
+    def run(cmd):
+        commands.append(cmd)
+        Path(cmd[cmd.index("-o") + 1]).write_bytes(b"")
+
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(shutil, "which", lambda name: None)
+    assert build.build().exists() and build.CEILING_OUT.exists()
+    assert not build.TORCH_OUT.exists()
+    assert "g++ is missing" in capsys.readouterr().err
+    assert all(c[0] == build.HIPCC for c in commands)

@@ -90,3 +90,13 @@ def test_same_errors(xr):
     assert e.value.status == xr.UNSUPPORTED
     with pytest.raises(KeyError):
         xr.allreduce_local([a], out, "nope")
+
+
+def test_same_results_without_the_module(xr, monkeypatch):
+    """Every call gives the same bytes through the Python code alone."""
+    fast = _calls(xr, lambda t: t, None)
+    assert not isinstance(xr._lib.native(), xr._lib._Declines)
+    monkeypatch.setattr(xr._lib, "_native", xr._lib._Declines())
+    slow = _calls(xr, lambda t: t, None)
+    for k, (a, b) in enumerate(zip(fast, slow)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), k
