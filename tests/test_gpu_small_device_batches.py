@@ -60,10 +60,12 @@ def test_first_small_batch_during_a_capture(xr, orc, K):
     for o in outs:
         o.zero_()
     xr.release()
-    work = torch.cuda.Stream()
+    # named, since torch hands out a pool's streams in turn: two in a row differ
+    capture, work = torch.cuda.Stream(), torch.cuda.Stream()
+    assert capture.cuda_stream != work.cuda_stream
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
+    with torch.cuda.graph(graph, stream=capture):
         xr.batched_reduce(citems, dtype="bf16")
         xr.batched_reduce(items, dtype="bf16", stream=work)
     torch.cuda.synchronize()
