@@ -41,7 +41,6 @@ template <class T>
 constexpr uint64_t tile_vecs() { return (uint64_t)kB * kU * kSub; }
 template <class T>
 constexpr uint64_t tile_elems() { return tile_vecs<T>() * T::kVec; }
-constexpr uint32_t kTileBytes = (uint32_t)kB * kU * kSub * 16u;
 constexpr uint32_t kSubBytes = (uint32_t)kB * kU * 16u;
 
 __device__ __forceinline__ bool item_runnable(const xred_item &it)
@@ -242,8 +241,11 @@ __device__ __forceinline__ void run_tile(const TileDesc &d, Mid &&mid)
                 for (int e = 0; e < T::kVec; ++e)
                     acc[h][e] = avg_scale<T, Op>(acc[h][e], d.nsrc);
             }
-            store_out(down_vec<T, Op>(acc[h]), d.dst + lb + toff, nrec,
-                      (uint32_t)(h * kB + threadIdx.x) * 16u);
+            char *base = d.dst + lb + toff;
+            const uint32_t o = (uint32_t)(h * kB + threadIdx.x) * 16u;
+            const u32x4 v = down_vec<T, Op>(acc[h]);
+            if (((uintptr_t)base & 15u) == 0) store_out<false>(v, base, nrec, o);
+            else store_out<true>(v, base, nrec, o);
         }
         if (!EARLY) ends();
         return;

@@ -64,16 +64,32 @@ __device__ __forceinline__ void bstore(u32x4 v, rsrc_t r, uint32_t off)
 }
 
 // One result vector, `o` bytes into a tile at `base` of which nrec bytes (whole
-// vectors) exist.  Off the 16-byte grid the vector is one unaligned
-// nontemporal store: the output is one stream of P + 1, and its misalignment
-// costs nothing that shows (P=8 bf16, output off the sources' grid, 4 / 16 / 128
+// vectors) exist.  OFF: off the 16-byte grid, where the vector is one unaligned
+// nontemporal store: the output is one stream of P + 1, and from HBM its
+// misalignment costs little (P=8 bf16, output off the sources' grid, 4 / 16 / 128
 // MiB per source: 7.0 / 25.0 / 186 us against 6.8 / 25.1 / 192 us on it;
 // realigning the results across lanes, with narrow stores at each wavefront's
-// ends, took 7.4 / 25.7 / 195).
+// ends, took 7.4 / 25.7 / 195; of calls that stay in the MALL only those around 4
+// MiB were faster realigned, P=6 and 7 3.6 and 3.9 us against 4.0 and 4.5).
+template <bool OFF>
 __device__ __forceinline__ void store_out(u32x4 v, char *base, uint32_t nrec, uint32_t o)
 {
-    if (((uintptr_t)base & 15u) == 0) bstore<kStoreOut>(v, make_rsrc(base, nrec), o);
-    else if (o < nrec) __builtin_nontemporal_store(v, (u32x4_any *)(base + o));
+    if constexpr (!OFF) {
+        bstore<kStoreOut>(v, make_rsrc(base, nrec), o);
+    } else {
+        // the vector stays above the test: sunk below it with its fold, it would
+        // keep every source's loads in registers (P=64 bf16: 254 VGPRs)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t w = v[i];
+            __asm__ volatile("" : "+v"(w));
+            v[i] = w;
+        }
+        // a global store also where the address came from another lane's registers
+        if (o < nrec)
+            __builtin_nontemporal_store(
+                v, (__attribute__((address_space(1))) u32x4_any *)(base + o));
+    }
 }
 
 // Bytes of a tile that exist: min(tile, total - off).
@@ -229,8 +245,9 @@ __device__ __forceinline__ void fold_groups(typename T::Acc (&acc)[T::kVec], con
 // 0 < NP <= 8: exactly NP sources, all loads issued before folding;
 // NP = 16, 32, 64: whole groups of 8, software pipelined;
 // NP == 0: any nsrc, in software-pipelined groups of 8 (fold_groups).
-// Every variant folds in source order 0..P-1.
-template <class T, class Op, int NP, int U, int B, class Src>
+// Every variant folds in source order 0..P-1.  OFF: dst + tl.off sits off the
+// 16-byte grid.
+template <class T, class Op, int NP, int U, int B, bool OFF = false, class Src>
 __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst, Tile tl)
 {
     typename T::Acc acc[U][T::kVec];
@@ -252,8 +269,8 @@ __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst,
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        store_out(down_vec<T, Op>(acc[u]), dst + tl.off, tl.nrec,
-                  (uint32_t)(u * B + threadIdx.x) * 16u);
+        store_out<OFF>(down_vec<T, Op>(acc[u]), dst + tl.off, tl.nrec,
+                       (uint32_t)(u * B + threadIdx.x) * 16u);
 }
 
 // Element i (scalar path): used for leads and tails shorter than a vector
@@ -468,42 +485,55 @@ __host__ __device__ __forceinline__ VecPlan vec_plan(uintptr_t s0, uintptr_t sdi
 
 // Work item i's tile when runs of kXcdRun consecutive tiles go to one XCD
 // (workgroup i runs on XCD i mod 8): within each block of 8 runs, XCD x takes
-// run x.  The last, partial block keeps its order.
-constexpr size_t kXcdRun = 32;
-__device__ __forceinline__ size_t xcd_run_tile(size_t i, size_t ntiles)
+// run x.  Work items from `end` on (xcd_run_end: the last, partial block) keep
+// their order.
+constexpr uint32_t kXcdRun = 32;
+constexpr int kRunsB = 128;   // largest workgroup whose tiles may go in runs
+__host__ __device__ __forceinline__ uint32_t xcd_run_end(uint32_t ntiles)
 {
-    if (i >= ntiles / (8 * kXcdRun) * (8 * kXcdRun)) return i;
+    return ntiles & ~(8 * kXcdRun - 1);
+}
+__device__ __forceinline__ uint32_t xcd_run_tile(uint32_t i, uint32_t end)
+{
+    if (i >= end) return i;
     return (i & ~(8 * kXcdRun - 1)) + (i & 7) * kXcdRun + ((i >> 3) & (kXcdRun - 1));
 }
 
 // ------------------------------------------------------ fused P-source --
-// dst[i] = fold_p src_p[i] for lead + nvec*kVec + tail elements, every
-// pointer at the same offset within 16 bytes: the first `lead` elements
-// (fewer than a vector) bring them all to a 16-byte boundary and, like the
-// last `tail` ones, are done by one workgroup, scalar; the nvec vectors
+// dst[i] = fold_p src_p[i] for lead + nvec*kVec + tail elements, every source
+// at the same offset within 16 bytes, dst too or (OFF) at another: the first
+// `lead` elements (fewer than a vector) bring the sources to a 16-byte boundary
+// and, like the last `tail` ones, are done by one workgroup, scalar; the nvec vectors
 // between go in tiles of B * U vectors (the last one ragged, cut by the buffer
 // range check).  `head` (a multiple of 16 below 128, at most nvec*16) is the
 // byte length of a first, short tile that ends where the first source
 // reaches a 128-byte line: the other tiles then start on line boundaries, so
 // no line is split between two tiles (whose workgroups, on different XCDs,
 // would each fetch it).
-// runs: tiles in runs of 32 per XCD (xcd_run_tile), else in address order.
-template <class T, class Op, int NP, int MAXP, int U, int B>
-__global__ __launch_bounds__(B) void reduce_vec_kernel(KernargSrc<MAXP> src, int nsrc, char *dst,
-                                                       size_t nvec, uint32_t tail, uint32_t head,
-                                                       uint32_t lead, bool runs)
+//
+// The first run_end tiles go in runs per XCD (xcd_run_tile; 0: all in address
+// order, as always in the larger workgroups).  A kernel argument and 32-bit
+// indices keep the loop's scalar registers few (int8 prod at P=8: 88 VGPRs with
+// 64-bit indices and the end computed per tile, 57 so).
+// OFF is a template parameter because both store forms in one kernel cost the
+// aligned one registers (int8 prod at P=8 61 -> 87 VGPRs, fp32 at P=64 36 bytes
+// of scratch).
+template <class T, class Op, int NP, int MAXP, int U, int B, bool OFF>
+__global__ __launch_bounds__(B) void reduce_vec_kernel(
+    KernargSrc<MAXP> src, int nsrc, char *dst, size_t nvec, uint32_t tail, uint32_t head,
+    uint32_t lead, uint32_t run_end)
 {
     constexpr uint32_t kTileBytes = (uint32_t)B * U * 16u;
     const size_t vbytes = nvec * 16;
     const size_t lb = (size_t)lead * T::kSize;   // bytes before the first vector
     const uint32_t first = head != 0 ? 1u : 0u;
-    const size_t ntiles = first + (vbytes - head + kTileBytes - 1) / kTileBytes;
-    for (size_t i = blockIdx.x; i < ntiles; i += gridDim.x) {
-        const size_t t = runs ? xcd_run_tile(i, ntiles) : i;
+    const uint32_t ntiles = first + (uint32_t)((vbytes - head + kTileBytes - 1) / kTileBytes);
+    for (uint32_t i = blockIdx.x; i < ntiles; i += gridDim.x) {
+        const uint32_t t = B <= kRunsB ? xcd_run_tile(i, run_end) : i;
         const bool h = t < first;
-        const size_t off = h ? 0 : head + (t - first) * kTileBytes;
-        reduce_tile<T, Op, NP, U, B>(src, nsrc, dst,
-                                     Tile{lb + off, h ? head : tile_nrec(vbytes, off, kTileBytes)});
+        const size_t off = h ? 0 : head + (size_t)(t - first) * kTileBytes;
+        reduce_tile<T, Op, NP, U, B, OFF>(
+            src, nsrc, dst, Tile{lb + off, h ? head : tile_nrec(vbytes, off, kTileBytes)});
     }
     if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)
         reduce_ends<T, Op>(src, nsrc, dst, lead, tail, lead + nvec * T::kVec);

@@ -148,9 +148,9 @@ __global__ __launch_bounds__(B) void reduce_offset_kernel(KernargSrc<XRED_MAX_SR
     constexpr uint32_t kTileBytes = (uint32_t)B * 16u;
     const size_t vbytes = nvec * 16;
     const size_t lb = (size_t)lead * T::kSize;
-    const size_t ntiles = (vbytes + kTileBytes - 1) / kTileBytes;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const size_t off = xcd_run_tile(t, ntiles) * kTileBytes;
+    const uint32_t ntiles = (uint32_t)((vbytes + kTileBytes - 1) / kTileBytes);
+    for (uint32_t i = blockIdx.x; i < ntiles; i += gridDim.x) {
+        const size_t off = (size_t)xcd_run_tile(i, xcd_run_end(ntiles)) * kTileBytes;
         offset_tile<T, Op>(src, nsrc, dst, lb, off, tile_nrec(vbytes, off, kTileBytes));
     }
     if ((tail | lead) != 0 && blockIdx.x == ntiles % gridDim.x)
@@ -195,9 +195,10 @@ hipError_t go_offset(const char *const *srcs, int nsrc, char *dst, size_t count,
                          ks, nsrc, dst, nvec, tail, vp.lead);
 }
 
-template <class T, class Op, int NP, int MAXP>
-hipError_t go_vec(const char *const *srcs, int nsrc, char *dst, size_t count, uint32_t lead,
-                  hipStream_t s)
+// OFF: dst off the grid of the sources' vectors.
+template <class T, class Op, int NP, int MAXP, bool OFF>
+hipError_t go_shape(const char *const *srcs, int nsrc, char *dst, size_t count, uint32_t lead,
+                    hipStream_t s)
 {
     KernargSrc<MAXP> ks;
     for (int p = 0; p < nsrc; ++p) ks.p[p] = srcs[p];
@@ -215,20 +216,31 @@ hipError_t go_vec(const char *const *srcs, int nsrc, char *dst, size_t count, ui
     const uint64_t one_round = (uint64_t)device_cus() * kWideWgsPerCu;
     const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
     if (tiles_wide <= one_round && (kFew || (cached && bytes > ((size_t)1 << 20))))
-        return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kBWide>,
+        return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kBWide, OFF>,
                              dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst, nvec,
-                             tail, head, lead, false);
+                             tail, head, lead, 0u);
     if constexpr (kFew) {
         const uint64_t tiles_wide2 = first + (nvec - hv + 2 * kBWide - 1) / (2 * kBWide) + extra;
         if (tiles_wide2 <= one_round && cached)
-            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 2, kBWide>,
+            return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 2, kBWide, OFF>,
                                  dim3(grid_for(tiles_wide2)), dim3(kBWide), 0, s, ks, nsrc, dst,
-                                 nvec, tail, head, lead, false);
+                                 nvec, tail, head, lead, 0u);
     }
     const uint64_t tiles = first + (nvec - hv + kB - 1) / kB + extra;
-    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kB>, dim3(grid_for(tiles)), dim3(kB),
-                         lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst, nvec,
-                         tail, head, lead, run_order(srcs, nsrc, dst, bytes));
+    const uint32_t run_end =
+        run_order(srcs, nsrc, dst, bytes) ? xcd_run_end((uint32_t)(tiles - extra)) : 0u;
+    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kB, OFF>, dim3(grid_for(tiles)),
+                         dim3(kB), lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst,
+                         nvec, tail, head, lead, run_end);
+}
+
+template <class T, class Op, int NP, int MAXP>
+hipError_t go_vec(const char *const *srcs, int nsrc, char *dst, size_t count, uint32_t lead,
+                  hipStream_t s)
+{
+    if ((((uintptr_t)dst + (size_t)lead * T::kSize) & 15u) == 0)
+        return go_shape<T, Op, NP, MAXP, false>(srcs, nsrc, dst, count, lead, s);
+    return go_shape<T, Op, NP, MAXP, true>(srcs, nsrc, dst, count, lead, s);
 }
 
 template <class T, class Op>

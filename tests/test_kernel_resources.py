@@ -1,0 +1,91 @@
+"""Registers and scratch of the built kernels, read from the code objects'
+metadata (no GPU needed).  The launch rules count on so many waves of a
+kernel fitting on a SIMD (512 VGPRs, in blocks of 8); a change that costs
+registers shows here, while results stay the same."""
+import re
+import struct
+import subprocess
+from pathlib import Path
+
+import pytest
+
+TOOLS = Path("/opt/rocm/llvm/bin")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_objects(fat):
+    """The gfx950 code objects of a .hip_fatbin section (a chain of offload bundles)."""
+    at = fat.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", fat, at + 24)
+        pos = at + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", fat, pos)
+            pos += 24
+            if size and b"gfx950" in fat[pos:pos + length]:
+                yield fat[at + off:at + off + size]
+            pos += length
+        at = fat.find(MAGIC, at + 1)
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: (VGPRs, bytes of scratch per lane)}"""
+    if not (TOOLS / "llvm-readelf").exists() or not (TOOLS / "llvm-objcopy").exists():
+        pytest.skip("no LLVM tools")
+    import paper_2510_20171_amd as xr
+    if not xr._lib.LIB_PATH.exists():
+        from paper_2510_20171_amd import build
+        build.build()
+    tmp = tmp_path_factory.mktemp("code")
+    subprocess.run([TOOLS / "llvm-objcopy", f"--dump-section=.hip_fatbin={tmp / 'fat'}",
+                    xr._lib.LIB_PATH, tmp / "copy"], check=True, timeout=100)
+    found = {}
+    for i, code in enumerate(_code_objects((tmp / "fat").read_bytes())):
+        path = tmp / f"{i}.co"
+        path.write_bytes(code)
+        notes = subprocess.run([TOOLS / "llvm-readelf", "--notes", path], check=True, timeout=100,
+                               capture_output=True, text=True).stdout
+        for block in notes.split("\n  - .agpr_count:")[1:]:
+            def field(key):
+                return re.search(rf"\.{key}:\s+(\S+)", block).group(1)  # noqa: B023
+            found[field("name")] = (int(field("vgpr_count")),
+                                    int(field("private_segment_fixed_size")))
+    assert len(found) > 1000
+    return found
+
+
+FUSED = re.compile(r"reduce_vec_kernelINS_\d+T(\w+?)ENS_\d+Op(\w+?)ELi(n?\d+)ELi\d+ELi(\d)ELi(\d+)"
+                   r"ELb([01])E")
+
+
+def _fused(kernels):
+    """(type, op, sources, vectors a thread, threads, output off the grid?, VGPRs, scratch)"""
+    out = []
+    for name, (vgprs, scratch) in kernels.items():
+        m = FUSED.search(name)
+        if m:
+            t, op, np_, u, b, off = m.groups()
+            out.append((t, op, int(np_.replace("n", "-")), int(u), int(b), off == "1", vgprs,
+                        scratch))
+    assert len(out) > 1000
+    return out
+
+
+def _waves(vgprs):
+    return 512 // max(8, -(-vgprs // 8) * 8)
+
+
+def test_outputs_on_the_grid_do_not_pay_for_the_others(kernels):
+    """Up to 8 sources and one vector a thread leave room for 7 waves per SIMD
+    in every type and op, and no count of sources needs scratch."""
+    bad = [k for k in _fused(kernels) if not k[5]
+           and (k[7] or (1 <= k[2] <= 8 and k[3] == 1 and _waves(k[6]) < 7))]
+    assert not bad, bad
+
+
+def test_outputs_off_the_grid_fold_as_they_load(kernels):
+    """Groups of sources are folded while later ones load there too: 64 sources
+    stay within 128 VGPRs (4 waves per SIMD, more than their launches' cap)."""
+    bad = [k for k in _fused(kernels) if k[5] and k[2] in (16, 32, 64) and _waves(k[6]) < 4]
+    assert not bad, bad
