@@ -187,19 +187,41 @@ __device__ __forceinline__ void fold_groups_pipelined(typename T::Acc (&acc)[U][
     }
 }
 
+// Any number of sources above 8, one group of loads at a time: groups of 8 and
+// an exact remainder.  One group in registers leaves room for 8 waves per SIMD,
+// which is what hides the loads in launches without a wave cap.
+template <class T, class Op, int U, int B, class Src>
+__device__ __forceinline__ void fold_groups(typename T::Acc (&acc)[U][T::kVec], const Src &src,
+                                            int nsrc, Tile tl)
+{
+    fold_group<T, Op, 8, U, B, true>(acc, src, 0, tl);
+    int p = 8;
+    for (; p + 8 <= nsrc; p += 8) fold_group<T, Op, 8, U, B, false>(acc, src, p, tl);
+    switch (nsrc - p) {
+    case 1: fold_group<T, Op, 1, U, B, false>(acc, src, p, tl); break;
+    case 2: fold_group<T, Op, 2, U, B, false>(acc, src, p, tl); break;
+    case 3: fold_group<T, Op, 3, U, B, false>(acc, src, p, tl); break;
+    case 4: fold_group<T, Op, 4, U, B, false>(acc, src, p, tl); break;
+    case 5: fold_group<T, Op, 5, U, B, false>(acc, src, p, tl); break;
+    case 6: fold_group<T, Op, 6, U, B, false>(acc, src, p, tl); break;
+    case 7: fold_group<T, Op, 7, U, B, false>(acc, src, p, tl); break;
+    default: break;
+    }
+}
+
 // This thread's vectors of 8 consecutive sources.
 struct Group8 {
     u32x4 v[8];
 };
 
 // Fold sources [p0, min(nsrc, p0 + 8)) into acc, in order; source 0 starts it.
-template <class T, class Op>
+template <class T, class Op, bool FULL>
 __device__ __forceinline__ void fold8(typename T::Acc (&acc)[T::kVec], const Group8 &g, int nsrc,
                                       int p0)
 {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        if (p0 + j < nsrc) {
+        if (FULL || p0 + j < nsrc) {
             if (j == 0 && p0 == 0) up_vec<T>(g.v[0], acc);
             else fold_vec<T, Op>(acc, g.v[j]);
         }
@@ -219,46 +241,57 @@ __device__ __forceinline__ void fetch8(Group8 &g, const Src &src, int nsrc, int 
     }
 }
 
-// Any number of sources, one vector per thread: groups of 8, the next group's
-// loads in flight while one is folded (fold order 0..nsrc-1).
+// Any number of sources above 8, one vector per thread: the next group's loads
+// in flight while one is folded (fold order 0..nsrc-1).  Twice the registers of
+// fold_groups (bf16 sum 94 VGPRs against 58, e4m3 125 against 79), so for
+// launches with few waves, whose time is one chain of loads.
 template <class T, class Op, class Src>
-__device__ __forceinline__ void fold_groups(typename T::Acc (&acc)[T::kVec], const Src &src,
-                                            int nsrc, Tile tl)
+__device__ __forceinline__ void fold_groups_ahead(typename T::Acc (&acc)[T::kVec], const Src &src,
+                                                  int nsrc, Tile tl)
 {
     Group8 a, b;
     fetch8(a, src, nsrc, 0, tl);
-    if (nsrc <= 8) {
-        fold8<T, Op>(acc, a, nsrc, 0);
-        return;
-    }
+#pragma nounroll
     for (int p0 = 0;; p0 += 16) {
         fetch8(b, src, nsrc, p0 + 8, tl);
-        fold8<T, Op>(acc, a, nsrc, p0);
-        if (p0 + 8 >= nsrc) return;
+        fold8<T, Op, true>(acc, a, nsrc, p0);
+        if (p0 + 16 >= nsrc) {
+            fold8<T, Op, false>(acc, b, nsrc, p0 + 8);
+            return;
+        }
         fetch8(a, src, nsrc, p0 + 16, tl);
-        fold8<T, Op>(acc, b, nsrc, p0 + 8);
-        if (p0 + 16 >= nsrc) return;
+        fold8<T, Op, true>(acc, b, nsrc, p0 + 8);
+        if (p0 + 24 >= nsrc) {
+            fold8<T, Op, false>(acc, a, nsrc, p0 + 16);
+            return;
+        }
     }
 }
+
+// Source counts known at launch only.
+constexpr int kAnyCount = 0, kAnyCountAhead = -1;
 
 // One tile: U vectors per thread at tile-relative vector u*B + threadIdx.x.
 // 0 < NP <= 8: exactly NP sources, all loads issued before folding;
 // NP = 16, 32, 64: whole groups of 8, software pipelined;
-// NP == 0: any nsrc, in software-pipelined groups of 8 (fold_groups).
+// NP == kAnyCount: any nsrc above 8, in groups of 8 (fold_groups);
+// NP == kAnyCountAhead: the same, the next group in flight (fold_groups_ahead).
 // Every variant folds in source order 0..P-1.  OFF: dst + tl.off sits off the
 // 16-byte grid.
 template <class T, class Op, int NP, int U, int B, bool OFF = false, class Src>
 __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst, Tile tl)
 {
     typename T::Acc acc[U][T::kVec];
-    if constexpr (NP > 8) {
+    if constexpr (NP == kAnyCountAhead) {
+        static_assert(U == 1, "one vector per thread");
+        fold_groups_ahead<T, Op>(acc[0], src, nsrc, tl);
+    } else if constexpr (NP == kAnyCount) {
+        fold_groups<T, Op, U, B>(acc, src, nsrc, tl);
+    } else if constexpr (NP > 8) {
         static_assert(NP % 8 == 0, "compile-time source counts above 8 are whole groups");
         fold_groups_pipelined<T, Op, NP / 8, U, B>(acc, src, tl);
-    } else if constexpr (NP > 0) {
-        fold_group<T, Op, NP, U, B, true>(acc, src, 0, tl);
     } else {
-        static_assert(U == 1, "runtime source counts take one vector per thread");
-        fold_groups<T, Op>(acc[0], src, nsrc, tl);
+        fold_group<T, Op, NP, U, B, true>(acc, src, 0, tl);
     }
     if constexpr (__is_same(Op, OpAvg)) {
         const int n = NP > 0 ? NP : nsrc;

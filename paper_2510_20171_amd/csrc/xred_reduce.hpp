@@ -24,13 +24,18 @@ namespace {
 //   with 128 threads; equal at 7 MiB).  More sources spread over the chip in
 //   128-thread workgroups (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us against
 //   8.1 / 23.6 / 41.6; P=16 512 KiB 3.1 against 4.3), except in the next case.
+//   Counts without a kernel of their own keep the next group of 8 sources in
+//   flight up to 1 MiB a source, where few waves hide the loads (bf16, rotating
+//   buffers, with / without: P=9, 24, 48 512 KiB 3.6 / 3.8, 4.7 / 5.2, 7.2 / 8.3 us;
+//   P=9 32 MiB 54.6 / 51.2).
 // * A call of at most 128 MiB of sources and output (half the MALL) mostly finds
 //   the last step's buffers there, and is then bound by dispatches and by what
 //   the wave cap keeps out rather than by HBM.  While they fit in one round, up to
 //   8 sources take 512-thread workgroups of two vectors a thread, and more
 //   sources past 1 MiB each those of one, uncapped (bf16, this / 128-thread tiles:
 //   P=2 12 MiB 4.3 / 6.8 us, P=4 9 / 16 MiB 7.3 / 8.2, 11.2 / 13.5, P=8 12 MiB
-//   15.6 / 18.3; P=9 4 MiB 5.8 / 9.2, P=16 2 / 4 MiB 5.2 / 5.4, 9.6 / 11.2).  Above
+//   15.6 / 18.3; P=9 4 MiB 5.6 / 7.7, P=12 2 / 4 MiB 4.5 / 4.6, 7.8 / 8.5, P=16 2 / 4
+//   MiB 5.2 / 5.4, 9.6 / 11.2, e4m3 P=16 4 MiB 10.9 / 12.1).  Above
 //   it the 128-thread tiles win where the data comes from HBM (P=8 16 MiB 25.2 /
 //   23.5).
 // * Larger launches are bandwidth-bound: 128-thread workgroups with a
@@ -65,6 +70,7 @@ namespace {
 constexpr int kB = 128;        // threads per workgroup, bandwidth-bound launches
 constexpr int kBWide = 512;    // threads per workgroup, one-round launches
 constexpr int kWideWgsPerCu = 4;   // resident 512-thread workgroups per CU
+constexpr size_t kAheadBytes = (size_t)1 << 20;      // a source of a latency-bound call
 constexpr size_t kCachedBytes = (size_t)128 << 20;   // sources and output of a MALL-sized call
 
 // One source stays in address order: a copy that fits the L2s is served from
@@ -215,7 +221,7 @@ hipError_t go_shape(const char *const *srcs, int nsrc, char *dst, size_t count, 
     constexpr bool kFew = NP >= 1 && NP <= 8;
     const uint64_t one_round = (uint64_t)device_cus() * kWideWgsPerCu;
     const uint64_t tiles_wide = first + (nvec - hv + kBWide - 1) / kBWide + extra;
-    if (tiles_wide <= one_round && (kFew || (cached && bytes > ((size_t)1 << 20))))
+    if (tiles_wide <= one_round && (kFew || (cached && bytes > kAheadBytes)))
         return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kBWide, OFF>,
                              dim3(grid_for(tiles_wide)), dim3(kBWide), 0, s, ks, nsrc, dst, nvec,
                              tail, head, lead, 0u);
@@ -229,9 +235,15 @@ hipError_t go_shape(const char *const *srcs, int nsrc, char *dst, size_t count, 
     const uint64_t tiles = first + (nvec - hv + kB - 1) / kB + extra;
     const uint32_t run_end =
         run_order(srcs, nsrc, dst, bytes) ? xcd_run_end((uint32_t)(tiles - extra)) : 0u;
-    return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 1, kB, OFF>, dim3(grid_for(tiles)),
-                         dim3(kB), lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst,
-                         nvec, tail, head, lead, run_end);
+    auto narrow = [&](auto kernel) {
+        return launch_kernel(kernel, dim3(grid_for(tiles)), dim3(kB),
+                             lds_for_waves(waves_for<T, NP>(bytes, nsrc)), s, ks, nsrc, dst, nvec,
+                             tail, head, lead, run_end);
+    };
+    if constexpr (NP == kAnyCount)
+        if (bytes <= kAheadBytes)
+            return narrow(reduce_vec_kernel<T, Op, kAnyCountAhead, MAXP, 1, kB, OFF>);
+    return narrow(reduce_vec_kernel<T, Op, NP, MAXP, 1, kB, OFF>);
 }
 
 template <class T, class Op, int NP, int MAXP>
@@ -284,7 +296,7 @@ hipError_t go(const char *const *srcs, int nsrc, char *dst, size_t count, hipStr
         break;
     default: break;
     }
-    return go_vec<T, Op, 0, XRED_MAX_SRC>(srcs, nsrc, dst, count, lead, s);
+    return go_vec<T, Op, kAnyCount, XRED_MAX_SRC>(srcs, nsrc, dst, count, lead, s);
 }
 
 

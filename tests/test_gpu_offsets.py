@@ -86,3 +86,15 @@ def test_cached_shapes(xr, orc, P, nbytes):
     for n in (nbytes // 16 * 8, nbytes // 16 * 8 + 9):
         for src, dst in ((0, 0), (1, 0)):
             _run(xr, orc, "bf16", "sum", P, n, [src] * P, dst, n)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3"])
+@pytest.mark.parametrize("P", [9, 15, 17, 24, 25])
+def test_runtime_counts(xr, orc, dtype, P):
+    """Source counts without a kernel of their own, on both sides of 1 MiB a
+    source (the next group of 8 in flight, then one group at a time) and, past
+    128 MiB in all, in the wave-capped shape; whole and partial last groups."""
+    es = np.dtype(gu.NP_BITS[dtype]).itemsize
+    for nbytes in (1 << 20, (1 << 20) + 16, (128 << 20) // (P + 1) + 32):
+        for src, dst in ((0, 0), (1, 0)):
+            _run(xr, orc, dtype, "sum", P, nbytes // es + src, [src] * P, dst, P)

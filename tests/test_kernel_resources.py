@@ -89,3 +89,15 @@ def test_outputs_off_the_grid_fold_as_they_load(kernels):
     stay within 128 VGPRs (4 waves per SIMD, more than their launches' cap)."""
     bad = [k for k in _fused(kernels) if k[5] and k[2] in (16, 32, 64) and _waves(k[6]) < 4]
     assert not bad, bad
+
+
+def test_counts_known_at_launch_keep_their_waves(kernels):
+    """Counts above 8 without a kernel of their own (0): the uncapped 512-thread
+    shape counts on 8 waves per SIMD (16 values a vector: 3).  With the next
+    group in flight (-1) they stay within the few waves such launches have."""
+    byte = ("E4M3", "E5M2", "I8", "U8")
+    got = [k for k in _fused(kernels) if k[2] in (0, -1)]
+    assert any(k[2] == -1 for k in got)
+    bad = [k for k in got if k[7] or _waves(k[6]) < (
+        3 if k[0] in byte or k[2] == -1 else 8 if k[4] == 512 else 6)]
+    assert not bad, bad
