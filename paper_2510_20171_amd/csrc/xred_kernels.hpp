@@ -533,6 +533,16 @@ __device__ __forceinline__ uint32_t xcd_run_tile(uint32_t i, uint32_t end)
 }
 
 // ------------------------------------------------------ fused P-source --
+// Waves per SIMD the compiler must leave room for (1: its own choice).  Two
+// vectors of 16 values each from 7 or 8 sources took 129-139 VGPRs, one
+// 512-thread workgroup per CU; under 128 two fit (e4m3 sum, P=8 12 MiB per
+// source: 18.3 -> 16.5 us; int8 max 17.0 -> 15.4).
+template <class T, int NP, int U, bool OFF>
+constexpr int reduce_min_waves()
+{
+    return U != 2 || T::kVec != 16 || OFF ? 1 : NP == 7 ? 5 : NP == 8 ? 4 : 1;
+}
+
 // dst[i] = fold_p src_p[i] for lead + nvec*kVec + tail elements, every source
 // at the same offset within 16 bytes, dst too or (OFF) at another: the first
 // `lead` elements (fewer than a vector) bring the sources to a 16-byte boundary
@@ -552,7 +562,7 @@ __device__ __forceinline__ uint32_t xcd_run_tile(uint32_t i, uint32_t end)
 // aligned one registers (int8 prod at P=8 61 -> 87 VGPRs, fp32 at P=64 36 bytes
 // of scratch).
 template <class T, class Op, int NP, int MAXP, int U, int B, bool OFF>
-__global__ __launch_bounds__(B) void reduce_vec_kernel(
+__global__ __launch_bounds__(B, (reduce_min_waves<T, NP, U, OFF>())) void reduce_vec_kernel(
     KernargSrc<MAXP> src, int nsrc, char *dst, size_t nvec, uint32_t tail, uint32_t head,
     uint32_t lead, uint32_t run_end)
 {

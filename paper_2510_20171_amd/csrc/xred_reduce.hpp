@@ -17,11 +17,12 @@ namespace {
 
 // Three tile shapes, one 16-byte vector of every source per thread but for the second:
 //
-// * Up to 8 sources, launches that fit on the chip in one round (every tile
-//   resident at once: up to 8 MiB per source) are latency-bound: 512-thread
-//   workgroups, uncapped, so the whole message is in flight after the fewest
-//   workgroup dispatches (P=8 bf16 4 MiB per source 6.8 us against 7.0-7.4
-//   with 128 threads; equal at 7 MiB).  More sources spread over the chip in
+// * Up to 8 sources, launches of at most four 512-thread workgroups per CU (up
+//   to 8 MiB per source) are latency-bound: 512-thread workgroups, uncapped, so
+//   the whole message is in flight after the fewest workgroup dispatches (P=8
+//   bf16 4 MiB per source 6.8 us against 7.0-7.4 with 128 threads; equal at 7
+//   MiB; e4m3 8 MiB 11.2 / 12.3).  All four are resident at once where a kernel
+//   takes at most 64 VGPRs, as these do.  More sources spread over the chip in
 //   128-thread workgroups (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us against
 //   8.1 / 23.6 / 41.6; P=16 512 KiB 3.1 against 4.3), except in the next case.
 //   Counts without a kernel of their own keep the next group of 8 sources in
@@ -30,14 +31,21 @@ namespace {
 //   P=9 32 MiB 54.6 / 51.2).
 // * A call of at most 128 MiB of sources and output (half the MALL) mostly finds
 //   the last step's buffers there, and is then bound by dispatches and by what
-//   the wave cap keeps out rather than by HBM.  While they fit in one round, up to
-//   8 sources take 512-thread workgroups of two vectors a thread, and more
-//   sources past 1 MiB each those of one, uncapped (bf16, this / 128-thread tiles:
-//   P=2 12 MiB 4.3 / 6.8 us, P=4 9 / 16 MiB 7.3 / 8.2, 11.2 / 13.5, P=8 12 MiB
-//   15.6 / 18.3; P=9 4 MiB 5.6 / 7.7, P=12 2 / 4 MiB 4.5 / 4.6, 7.8 / 8.5, P=16 2 / 4
-//   MiB 5.2 / 5.4, 9.6 / 11.2, e4m3 P=16 4 MiB 10.9 / 12.1).  Above
-//   it the 128-thread tiles win where the data comes from HBM (P=8 16 MiB 25.2 /
-//   23.5).
+//   the wave cap keeps out rather than by HBM.  Up to the same number of
+//   workgroups, up to 8 sources take 512-thread ones of two vectors a thread while
+//   the call has at most 108 MiB, and more sources past 1 MiB each those of one,
+//   uncapped (bf16, this / 128-thread tiles: P=2 12 MiB 4.3 / 6.8 us, P=4 9 / 16 MiB
+//   7.3 / 8.2, 11.2 / 12.1, P=8 12 MiB 15.3 / 16.9, e4m3 16.5 / 17.5; P=9 4 MiB 5.6 /
+//   7.7, P=12 2 / 4 MiB 4.5 / 4.6, 7.8 / 8.5, P=16 2 / 4 MiB 5.2 / 5.4, 9.6 / 11.2,
+//   e4m3 P=16 4 MiB 10.9 / 12.1).  108 MiB is 12 MiB of 8 sources: there two vectors a thread make three whole workgroups per CU; at
+//   13 to 15 MiB, a broken fourth, the 128-thread tiles win warm and from HBM (two
+//   vectors / 128 threads, back to back and rotating buffers: 13 MiB 18.4 / 17.3,
+//   21.6 / 20.0 us; 14 MiB 19.9 / 19.2, 22.9 / 21.3; e4m3 13 MiB 19.4 / 18.1, 22.5 / 20.6).
+//   At 16 MiB it depends on the buffers' addresses: 16 MiB apart 22.3 / 23.6, 25.1 /
+//   24.3; with 4 KiB, 1 MiB or 2 MiB more between them 21.8 / 22.6, 22.4 / 21.0 and
+//   22.3 / 22.3 back to back, 24.4 / 24.6, 25.2 / 24.0 and 25.0 / 23.9 rotating.
+//   Outputs off the sources' grid keep two vectors to 128 MiB (P=8 14 MiB 20.8 / 21.5
+//   back to back; P=7 16 MiB 20.6 / 22.3).
 // * Larger launches are bandwidth-bound: 128-thread workgroups with a
 //   bounded number of waves per CU.  HBM3E on MI355X delivers the most when
 //   a CU keeps a moderate number of loads in flight; more waves than that
@@ -69,9 +77,11 @@ namespace {
 // 48.8, 128 MiB 104.7 / 106.2; P=32 16 MiB 86.6 / 86.8, 32 MiB 169.3 / 173.4).
 constexpr int kB = 128;        // threads per workgroup, bandwidth-bound launches
 constexpr int kBWide = 512;    // threads per workgroup, one-round launches
-constexpr int kWideWgsPerCu = 4;   // resident 512-thread workgroups per CU
+constexpr int kWideWgsPerCu = 4;   // most 512-thread workgroups per CU of one-round launches
 constexpr size_t kAheadBytes = (size_t)1 << 20;      // a source of a latency-bound call
 constexpr size_t kCachedBytes = (size_t)128 << 20;   // sources and output of a MALL-sized call
+template <bool OFF>
+constexpr size_t kTwoVecBytes = (size_t)(OFF ? 128 : 108) << 20;   // the same, two vectors a thread
 
 // One source stays in address order: a copy that fits the L2s is served from
 // them when an XCD meets its last call's lines (20 MiB 5.2 us, in runs 7.1).
@@ -227,7 +237,7 @@ hipError_t go_shape(const char *const *srcs, int nsrc, char *dst, size_t count, 
                              tail, head, lead, 0u);
     if constexpr (kFew) {
         const uint64_t tiles_wide2 = first + (nvec - hv + 2 * kBWide - 1) / (2 * kBWide) + extra;
-        if (tiles_wide2 <= one_round && cached)
+        if (tiles_wide2 <= one_round && bytes <= kTwoVecBytes<OFF> / ((size_t)nsrc + 1))
             return launch_kernel(reduce_vec_kernel<T, Op, NP, MAXP, 2, kBWide, OFF>,
                                  dim3(grid_for(tiles_wide2)), dim3(kBWide), 0, s, ks, nsrc, dst,
                                  nvec, tail, head, lead, 0u);

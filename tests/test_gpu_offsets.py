@@ -98,3 +98,15 @@ def test_runtime_counts(xr, orc, dtype, P):
     for nbytes in (1 << 20, (1 << 20) + 16, (128 << 20) // (P + 1) + 32):
         for src, dst in ((0, 0), (1, 0)):
             _run(xr, orc, dtype, "sum", P, nbytes // es + src, [src] * P, dst, P)
+
+
+@pytest.mark.parametrize("dtype,op", [("bf16", "sum"), ("e4m3", "sum"), ("i8", "max")])
+@pytest.mark.parametrize("P", [7, 8])
+def test_two_vector_limit(xr, orc, dtype, op, P):
+    """Up to 8 sources at the size up to which a thread takes two vectors:
+    108 MiB of sources and output (128 MiB off the sources' grid)."""
+    es = np.dtype(gu.NP_BITS[dtype]).itemsize
+    for src, limit in ((0, 108 << 20), (1, 128 << 20)):
+        for extra in (0, 16):
+            n = (limit // (P + 1) + extra) // es
+            _run(xr, orc, dtype, op, P, n, [src] * P, 0, n)

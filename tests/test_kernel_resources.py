@@ -101,3 +101,10 @@ def test_counts_known_at_launch_keep_their_waves(kernels):
     bad = [k for k in got if k[7] or _waves(k[6]) < (
         3 if k[0] in byte or k[2] == -1 else 8 if k[4] == 512 else 6)]
     assert not bad, bad
+
+
+def test_two_vectors_a_thread_leave_two_workgroups_per_cu(kernels):
+    """Two vectors of each source a thread: two 512-thread workgroups of every
+    type fit on a CU (4 waves per SIMD), without scratch."""
+    bad = [k for k in _fused(kernels) if k[3] == 2 and (k[7] or _waves(k[6]) < 4)]
+    assert not bad, bad

@@ -76,3 +76,29 @@ def test_trace_logs_launches():
     launch = [l for l in lines if l.startswith("[xred] launch ")]
     assert len(launch) == 1, lines
     assert "reduce_vec_kernel" in launch[0] and launch[0].endswith("-> hipSuccess"), launch
+
+
+SHAPES = """
+import torch
+import paper_2510_20171_amd as xr
+src = [torch.ones((14 << 20) // 2 + 8, dtype=torch.bfloat16, device="cuda") for _ in range(8)]
+out = torch.empty_like(src[0])
+for mib, off in ((12, 0), (13, 0), (13, 1)):
+    n = (mib << 20) // 2
+    xr.allreduce_local([s[:n] for s in src], out[off:off + n])
+torch.cuda.synchronize()
+"""
+
+
+@pytest.mark.gpu
+def test_trace_shows_the_fused_shapes():
+    """Workgroup sizes on both sides of the two-vector limit (8 sources of 12
+    MiB; further off the sources' grid)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    r = run(SHAPES, "1")
+    assert r.returncode == 0, r.stderr
+    launch = [l for l in r.stderr.splitlines() if l.startswith("[xred] launch ")]
+    print("\n".join(launch))
+    assert ["block=512" in l for l in launch[:3]] == [True, False, True], launch
