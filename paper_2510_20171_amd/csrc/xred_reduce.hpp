@@ -57,10 +57,12 @@ namespace {
 //   workgroup an LDS reservation it never touches, sized so that only the
 //   wanted number of workgroups fit on a CU.
 // * Five to eight sources want more loads in flight when each holds several
-//   hundred MiB, and when a launch is only a few rounds long (P=8 bf16: 9 / 11 /
-//   13 / 16 / 24 MiB in runs at 12 waves 14.3 / 17.1 / 19.6 / 23.5 / 34.1 us, at
-//   16 waves 14.0 / 16.7 / 19.5 / 23.4 / 34.5; 32 MiB and 128 MiB 12; 256 MiB
-//   16, 360 us against 374 us; 512 MiB 24, 830 us against 963 us; 768 MiB 20-24,
+//   hundred MiB, and when a launch is only a few rounds long (12 / 16 / 20 / 24
+//   waves, back to back: P=5 bf16 17 MiB 16.7 / 15.3 / 15.1 / 15.1 us, 24 MiB 24.1 /
+//   23.2 / 23.1 / 23.0; P=6 24 MiB 27.9 / 26.7 / 26.8 / 26.8; P=7 24 MiB 29.5 / 28.2 / 28.2 /
+//   28.7; P=8 17 MiB 22.9 / 22.5 / 22.7 / 23.1, 24 MiB 33.3 / 33.5 / 33.6 / 33.9; P=8 e4m3
+//   17 MiB 25.0 / 23.7 / 23.4 / 23.8, int8 24 MiB 35.3 / 32.2 / 32.9 / 33.1, fp32 within 1 %
+//   of bf16); P=8 32 MiB and 128 MiB 12; 256 MiB 16, 360 us against 374 us; 512 MiB 24, 830 us against 963 us; 768 MiB 20-24,
 //   1232 us against 1346 us).  16 and 32 sources keep their caps up to 4.4 GB.
 //
 // Tile order of the 128-thread shape.  In address order, with one 2 KiB tile
@@ -203,10 +205,14 @@ hipError_t go_offset(const char *const *srcs, int nsrc, char *dst, size_t count,
     const size_t bytes = count * T::kSize, nvec = vp.nvec;
     const uint32_t tail = (uint32_t)(count - vp.lead - nvec * T::kVec);
     const dim3 grid(grid_for((nvec + kB - 1) / kB + ((tail | vp.lead) ? 1 : 0)));
-    // 12 waves also for 5-8 sources of at most 24 MiB, unlike the vector path
-    // (mixed offsets at 19 MiB, 12 / 16 / 24 waves: 28.3 / 29.0 / 30.6 us)
+    // 5 and 6 sources want 16 waves up to 192 MiB, 7 and 8 want 12, in every type,
+    // also where the vector path takes others (mixed offsets, 12 / 16 / 20 waves:
+    // bf16 P=5 19 / 64 / 128 MiB 22.1 / 19.4 / 19.6, 66.5 / 59.6 / 60.3, 131.3 / 119.7 /
+    // 121.2 us, P=6 64 MiB 72.9 / 68.9 / 70.1, int8 P=5 128 MiB 137.5 / 129.1 / -; P=7
+    // 64 MiB 80.5 / 82.9 / 84.9, P=8 19 / 128 MiB 28.2 / 29.1 / 29.9, 181.4 / 190.0 /
+    // 194.2, f16 avg, fp32, e4m3 and int8 alike)
     const int waves = nsrc >= 5 && nsrc <= 8 && bytes <= ((size_t)192 << 20)
-                          ? 12 : waves_split<T>(bytes, nsrc);
+                          ? (nsrc <= 6 ? 16 : 12) : waves_split<T>(bytes, nsrc);
     return launch_kernel(reduce_offset_kernel<T, Op, kB>, grid, dim3(kB), lds_for_waves(waves), s,
                          ks, nsrc, dst, nvec, tail, vp.lead);
 }

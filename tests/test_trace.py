@@ -102,3 +102,29 @@ def test_trace_shows_the_fused_shapes():
     launch = [l for l in r.stderr.splitlines() if l.startswith("[xred] launch ")]
     print("\n".join(launch))
     assert ["block=512" in l for l in launch[:3]] == [True, False, True], launch
+
+
+OFFSETS = """
+import torch
+import paper_2510_20171_amd as xr
+src = [torch.ones((64 << 10) + 8, dtype=torch.bfloat16, device="cuda") for _ in range(8)]
+out = torch.empty(64 << 10, dtype=torch.bfloat16, device="cuda")
+for p in (5, 6, 7, 8):
+    xr.allreduce_local([s[k % 3:][:64 << 10] for k, s in enumerate(src[:p])], out)
+torch.cuda.synchronize()
+"""
+
+
+@pytest.mark.gpu
+def test_trace_shows_the_wave_caps_at_offsets():
+    """Sources at different offsets: the LDS reservation leaves room for 8
+    workgroups of 2 waves per CU with 5 and 6 sources, for 6 with 7 and 8."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    r = run(OFFSETS, "1")
+    assert r.returncode == 0, r.stderr
+    launch = [l for l in r.stderr.splitlines() if l.startswith("[xred] launch ")]
+    assert len(launch) == 4 and all("reduce_offset_kernel" in l for l in launch), launch
+    lds = [int(l.split(" lds=")[1].split()[0]) for l in launch]
+    assert [(160 << 10) // x for x in lds] == [8, 8, 6, 6], launch
