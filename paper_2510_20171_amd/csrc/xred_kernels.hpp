@@ -599,36 +599,62 @@ __global__ __launch_bounds__(B) void reduce_scalar_kernel(KernargSrc<XRED_MAX_SR
 // contiguous for every type.  (With a 16-byte input vector per thread the
 // lanes of a narrow type stepped 32 or 64 bytes through the accumulator,
 // four fifths of a step's bytes and more: bf16 4M elements 7.05 us a step
-// against 6.0 now, e4m3 9.3 against 5.4, both 6.7 TB/s now.)  Input and
-// output parts may sit at any element offset: they go through global accesses
-// the hardware realigns (chunks cut at odd lengths: bf16 4M elements 11 us
-// element by element, 6.3 now); the accumulator's buffer accesses need only
-// 4-byte alignment, which every accumulator has.
+// against 6.0 now, e4m3 9.3 against 5.4, both 6.7 TB/s now.)
+//
+// Input and output parts may sit at any element offset.  Buffer accesses need
+// only 4-byte alignment, which every accumulator and every part of a 4- or
+// 8-byte type has; narrower types' input goes through global loads the hardware
+// realigns, their output through device-scope buffer stores where it is 4-byte
+// aligned and ordinary global stores elsewhere.  (4M elements, global accesses
+// under per-lane tests throughout: fp32 plain step / FINAL / cast 7.6 / 7.5 / 5.1 us,
+// 7.1 / 6.85 / 3.85 so, fp64 16.0 / 16.4 / 12.8 and 15.9 / 15.6 / 10.0; bf16 16M
+// FINAL / cast 20.5 / 17.9 and 19.7 / 14.6.  bf16 chunks cut at odd lengths, 4M: 11
+// us element by element, 6.3 now.)
+
 // Input or output bytes of one accumulator vector.
 template <class T>
 constexpr int part_bytes() { return acc_per_vec<T>() * T::kSize; }
 
-// The part at p (any alignment) in the low words of a vector, the others 0.
-template <int BYTES>
-__device__ __forceinline__ u32x4 load_part(const char *p)
+// Input part q of a tile at `base` that holds n > 0 of them, in the low words of
+// a vector, the others 0.  Parts of types of 4 and 8 bytes are 4-byte aligned,
+// which is all a buffer load needs, and past the end read 0; narrower types'
+// parts lie anywhere, and lanes past the end read part 0.
+template <class T>
+__device__ __forceinline__ u32x4 load_part(const char *base, uint32_t n, uint32_t q)
 {
+    constexpr int BYTES = part_bytes<T>();
     static_assert(BYTES == 4 || BYTES == 8 || BYTES == 16, "whole accumulator vectors");
-    if constexpr (BYTES == 16) {
-        return __builtin_nontemporal_load((const u32x4_any *)p);
-    } else if constexpr (BYTES == 8) {
-        const u32x2 x = __builtin_nontemporal_load((const u32x2_any *)p);
-        return u32x4{x[0], x[1], 0u, 0u};
+    if constexpr (T::kSize >= 4) {
+        return bload<kLoadStream>(make_rsrc(base, n * 16u), q * 16u);
     } else {
-        return u32x4{__builtin_nontemporal_load((const u32_any *)p), 0u, 0u, 0u};
+        const char *p = base + (size_t)(q < n ? q : 0u) * BYTES;
+        if constexpr (BYTES == 8) {
+            const u32x2 x = __builtin_nontemporal_load((const u32x2_any *)p);
+            return u32x4{x[0], x[1], 0u, 0u};
+        } else {
+            return u32x4{__builtin_nontemporal_load((const u32_any *)p), 0u, 0u, 0u};
+        }
     }
 }
 
-template <int BYTES>
-__device__ __forceinline__ void store_part(u32x4 v, char *p)
+// Output part q of such a tile; parts past the end are not stored.
+template <class T>
+__device__ __forceinline__ void store_part(u32x4 v, char *base, uint32_t n, uint32_t q)
 {
-    if constexpr (BYTES == 16) *(u32x4_any *)p = v;
-    else if constexpr (BYTES == 8) *(u32x2_any *)p = u32x2{v[0], v[1]};
-    else *(u32_any *)p = v[0];
+    constexpr int BYTES = part_bytes<T>();
+    if constexpr (T::kSize >= 4) {
+        bstore<kStoreOut>(v, make_rsrc(base, n * 16u), q * 16u);
+    } else if (((uintptr_t)base & 3u) == 0) {
+        const rsrc_t r = make_rsrc(base, n * BYTES);
+        if constexpr (BYTES == 8)
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{v[0], v[1]}, r, q * 8u, 0, kStoreOut);
+        else
+            __builtin_amdgcn_raw_buffer_store_b32(v[0], r, q * 4u, 0, kStoreOut);
+    } else if (q < n) {
+        char *p = base + (size_t)q * BYTES;
+        if constexpr (BYTES == 8) *(u32x2_any *)p = u32x2{v[0], v[1]};
+        else *(u32_any *)p = v[0];
+    }
 }
 
 // The first PV values of a vector's up(), and down() of PV values into its
@@ -668,8 +694,7 @@ __device__ __forceinline__ void step_tile(const char *in, char *acc, char *dst, 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t q = (uint32_t)u * B + threadIdx.x;
-        x[u] = u32x4{};
-        if (q < n) x[u] = load_part<PB>(in + (v0 + q) * PB);
+        x[u] = load_part<T>(in + v0 * PB, n, q);
     }
     if constexpr (!kInit) {
 #pragma unroll
@@ -684,7 +709,7 @@ __device__ __forceinline__ void step_tile(const char *in, char *acc, char *dst, 
 #pragma unroll
         for (int j = 0; j < PV; ++j) a[u][j] = kInit ? b[j] : combine<T, Op>(a[u][j], b[j]);
         if constexpr (kFinal) {
-            if (q < n) store_part<PB>(down_part<T, Op>(a[u]), dst + (v0 + q) * PB);
+            store_part<T>(down_part<T, Op>(a[u]), dst + v0 * PB, n, q);
         } else {
 #pragma unroll
             for (int j = 0; j < PV; ++j) a[u][j] = finalize<T, Op>(a[u][j]);
@@ -745,7 +770,7 @@ __global__ __launch_bounds__(B) void acc_cast_kernel(const char *acc, char *dst,
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t q = (uint32_t)u * B + threadIdx.x;
-            if (q < n) store_part<PB>(down_part<T, OpSum>(a[u]), dst + (v0 + q) * PB);
+            store_part<T>(down_part<T, OpSum>(a[u]), dst + v0 * PB, n, q);
         }
     }
     if (tail != 0 && blockIdx.x == ntiles % gridDim.x && threadIdx.x < tail) {

@@ -1,7 +1,8 @@
-"""Registers and scratch of the built kernels, read from the code objects'
-metadata (no GPU needed).  The launch rules count on so many waves of a
-kernel fitting on a SIMD (512 VGPRs, in blocks of 8); a change that costs
-registers shows here, while results stay the same."""
+"""Registers, scratch and memory instructions of the built kernels, read from
+the code objects (no GPU needed).  The launch rules count on so many waves of
+a kernel fitting on a SIMD (512 VGPRs, in blocks of 8), the streaming kernels
+on buffer accesses with their cache policy; a change that costs either shows
+here, while results stay the same."""
 import re
 import struct
 import subprocess
@@ -29,8 +30,8 @@ def _code_objects(fat):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{mangled name: (VGPRs, bytes of scratch per lane)}"""
+def code_objects(tmp_path_factory):
+    """The library's code objects as files."""
     if not (TOOLS / "llvm-readelf").exists() or not (TOOLS / "llvm-objcopy").exists():
         pytest.skip("no LLVM tools")
     import paper_2510_20171_amd as xr
@@ -40,10 +41,18 @@ def kernels(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("code")
     subprocess.run([TOOLS / "llvm-objcopy", f"--dump-section=.hip_fatbin={tmp / 'fat'}",
                     xr._lib.LIB_PATH, tmp / "copy"], check=True, timeout=100)
-    found = {}
+    paths = []
     for i, code in enumerate(_code_objects((tmp / "fat").read_bytes())):
-        path = tmp / f"{i}.co"
-        path.write_bytes(code)
+        paths.append(tmp / f"{i}.co")
+        paths[-1].write_bytes(code)
+    return paths
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    """{mangled name: (VGPRs, bytes of scratch per lane)}"""
+    found = {}
+    for path in code_objects:
         notes = subprocess.run([TOOLS / "llvm-readelf", "--notes", path], check=True, timeout=100,
                                capture_output=True, text=True).stdout
         for block in notes.split("\n  - .agpr_count:")[1:]:
@@ -108,3 +117,25 @@ def test_two_vectors_a_thread_leave_two_workgroups_per_cu(kernels):
     type fit on a CU (4 waves per SIMD), without scratch."""
     bad = [k for k in _fused(kernels) if k[3] == 2 and (k[7] or _waves(k[6]) < 4)]
     assert not bad, bad
+
+
+def test_steps_of_wide_types_use_buffer_accesses(code_objects, kernels):
+    """Closing casts and FINAL steps of 4- and 8-byte types store whole vectors
+    at device scope, and plain steps load theirs, through buffer descriptors:
+    per-lane tests and ordinary stores took 4 to 30 % more."""
+    wide = r"NS_\d+T(F32|I32|U32|F64|I64|U64)E"
+    stores = [n for n in kernels if re.search(rf"(acc_cast_kernelI{wide}|step_kernelI{wide}"
+                                              r"NS_\d+OpSumELj[23]E)", n)]
+    loads = [n for n in kernels if re.search(rf"step_kernelI{wide}NS_\d+OpSumELj0E", n)]
+    assert len(stores) == 18 and len(loads) == 6, (stores, loads)
+    text = ""
+    for path in code_objects:
+        text += subprocess.run([TOOLS / "llvm-objdump", "-d", "--disassemble-symbols="
+                                + ",".join(stores + loads), path], check=True, timeout=100,
+                               capture_output=True, text=True).stdout
+    body = dict(re.findall(r"<(\w+)>:\n(.*?)(?=\n[0-9a-f]+ <|\Z)", text, re.S))
+    for n in stores:
+        assert len(re.findall(r"buffer_store_dwordx4 .* sc1", body[n])) >= 2, n
+        assert "global_store_dwordx4" not in body[n] and "flat_store_dwordx4" not in body[n], n
+    for n in loads:      # the input's two vectors and the accumulator's
+        assert len(re.findall(r"buffer_load_dwordx4", body[n])) >= 4, n
