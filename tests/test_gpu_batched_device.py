@@ -1,5 +1,5 @@
 """Device-resident batch descriptors past one run of items (the queue and
-grouped kernels).
+runs kernels).
 
 A batch of more than 64 items whose descriptors live in device memory runs,
 when launched eagerly, on the queue kernel: a persistent grid whose
@@ -9,7 +9,7 @@ counters used alternately by successive launches on the stream).  Under
 graph capture, or past the queue's 16384 items, the batch is cut into runs
 of consecutive items, each run dealt tile by tile to its own set of
 workgroups that plan their tiles from the descriptors in the kernel (the
-grouped kernel).  These tests drive both paths across their boundaries
+runs kernel).  These tests drive both paths across their boundaries
 against the CPU oracle:
 
 - batch sizes on both sides of whole runs (65, 127, 128, 129 items) and many
@@ -201,7 +201,7 @@ def test_device_batch_queue_item_limit(xr, orc, K):
     """K int32 items of 1..40 elements over two sources, laid end to end, so
     the concatenated outputs equal one oracle reduction of the concatenated
     sources: the largest batch the queue kernel plans in LDS, and one more
-    item (the grouped kernel)."""
+    item (the runs kernel)."""
     rng = np.random.default_rng(5500 + K)
     sizes = rng.integers(1, 41, size=K)
     sizes[-1] = 3 * 512 * 4 + 1             # the last item spans several tiles

@@ -128,10 +128,12 @@ def test_batched_table_at_its_limit(xr, orc):
     torch.cuda.empty_cache()
 
 
-def test_device_batch_with_an_item_past_4gib(xr, orc):
-    """Device descriptors, 70 items (two runs of the grouped kernel): item 0
-    holds 2^31 + 5 bf16 elements per source (past 4 GiB, over 2^19 tiles), the
-    others up to 9000; sampled columns of item 0, every other item whole."""
+@pytest.mark.parametrize("captured", [False, True])
+def test_device_batch_with_an_item_past_4gib(xr, orc, captured):
+    """Device descriptors, 70 items: item 0 holds 2^31 + 5 bf16 elements per
+    source (past 4 GiB, 2^18 tiles), the others up to 9000; launched eagerly
+    (the queue kernel) and replayed from a graph (two runs of the runs kernel).
+    Sampled columns of item 0, every other item whole."""
     n0 = (1 << 31) + 5
     big = [_random_bits(n0, 2, 1700 + p) for p in range(2)]
     out0 = torch.empty(n0, dtype=torch.int16, device="cuda")
@@ -149,8 +151,21 @@ def test_device_batch_with_an_item_past_4gib(xr, orc):
     arr = np.zeros(len(rows), xr.ITEM_DTYPE)
     for k, r in enumerate(rows):
         arr[k] = r
-    xr.batched_reduce(torch.from_numpy(arr.view(np.uint8).copy()).to("cuda"), "sum",
-                      dtype="bf16")
+    items = torch.from_numpy(arr.view(np.uint8).copy()).to("cuda")
+    if captured:
+        xr.batched_reduce(items, "sum", dtype="bf16")   # the kernels are loaded
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            xr.batched_reduce(items, "sum", dtype="bf16")
+        for _ in range(2):
+            for out in [out0] + [o for _, o in small]:
+                out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+    else:
+        xr.batched_reduce(items, "sum", dtype="bf16")
     torch.cuda.synchronize()
     idx = _samples(n0, 2, np.random.default_rng(32))
     cols = [gu.bits(s[idx], "bf16").copy() for s in big]
