@@ -9,13 +9,14 @@
 //   table        (host descriptors, the usual case): the host stages the
 //                item of every tile and one workgroup runs each tile, so the
 //                hardware dispatches tiles in order, as for the fused kernel;
-//   queue        (device descriptors, eager): a persistent grid takes tiles
-//                in order from a counter in device memory;
-//   runs         (device descriptors under graph capture, or past the queue's
-//                limits): runs of up to 64 consecutive items, each dealt tile
-//                by tile to its own set of workgroups, whose waves plan their
-//                tiles from the descriptors in registers (metadata by
-//                reference, Section 6.1); no state between calls;
+//   queue        (device descriptors of more than 64 items, eager): a persistent
+//                grid takes tiles in order from a counter in device memory;
+//   runs         (other device descriptors: up to 64 items, under graph
+//                capture, or past the queue's limits): runs of up to 64
+//                consecutive items, each dealt tile by tile to its own set of
+//                workgroups, whose waves plan their tiles from the descriptors
+//                in registers (metadata by reference, Section 6.1); no state
+//                between calls;
 //   round-robin  (host batches past the table's size): a persistent grid,
 //                tile g on workgroup g mod G, the tile-start prefix staged;
 //   range        (host batches past the round-robin plan's items): contiguous

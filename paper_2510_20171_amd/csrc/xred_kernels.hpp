@@ -2,16 +2,17 @@
 //
 // All kernels stream 16-byte vectors: one wavefront covers 64 lanes x 16 B =
 // 1 KiB of every source per vector step, and each thread keeps U vectors of
-// every source in flight before folding (the fold order over sources is the
-// fixed left fold 0..P-1 whatever the load order).
+// every source, or of a group of 8, in flight before folding (the fold order over
+// sources is the fixed left fold 0..P-1 whatever the load order).
 //
-// Memory is accessed through buffer resource descriptors built per tile
-// (base = stream + tile offset, num_records = bytes of the tile that exist).
-// The hardware range check then replaces per-lane bounds tests: loads past
+// Memory on the 16-byte grid is accessed through buffer resource descriptors
+// built per tile (base = stream + tile offset, num_records = bytes of the tile
+// that exist).  The hardware range check then replaces per-lane bounds tests: loads past
 // num_records return 0 and stores past it are dropped, so the ragged last
 // tile runs the same straight-line code as every other tile.  Buffer
-// instructions also always address global memory (no flat accesses when
-// pointers come from device-side descriptors) and carry the cache policy:
+// instructions also always address global memory, wherever the pointer came
+// from, and carry the cache policy.  (Vectors off the grid, and the parts of
+// narrow types' steps, take global accesses the hardware realigns.)  The policy:
 // sources are read nontemporally (each byte is used once); outputs are
 // written with device-scope (sc1) stores, which measured 2-5 % faster on
 // MI355X for this 8:1 read/write mix than ordinary write-back stores and
@@ -19,9 +20,10 @@
 // ordinary loads and stores, which may leave it in the MALL between
 // launches (not in L2: a launch starts with its L2 lines invalidated).
 //
-// Work is split into tiles of B*U vectors.  Tile t is processed by workgroup
-// t mod gridDim.x, so with a fixed grid a tile always lands on the same XCD
-// (workgroups are dispatched to the 8 XCDs round-robin).
+// Work is split into tiles of B*U vectors.  Work item i is processed by
+// workgroup i mod gridDim.x, so with a fixed grid it always lands on the same XCD
+// (workgroups are dispatched to the 8 XCDs round-robin); it is tile i, or with
+// runs per XCD another tile of its block (xcd_run_tile).
 #pragma once
 
 #include "xred_device.hpp"
@@ -306,9 +308,9 @@ __device__ __forceinline__ void reduce_tile(const Src &src, int nsrc, char *dst,
                        (uint32_t)(u * B + threadIdx.x) * 16u);
 }
 
-// Element i (scalar path): used for leads and tails shorter than a vector
-// and for buffers at different offsets within 16 bytes.  The loads of up to
-// 8 sources are issued before they are folded, in source order.
+// Element i (scalar path): leads and tails shorter than a vector, and calls
+// without a whole vector.  The loads of up to 8 sources are issued before they
+// are folded, in source order.
 template <class T, class Op, class Src>
 __device__ __forceinline__ void reduce_elem(const Src &src, int nsrc, char *dst, size_t i)
 {
@@ -420,7 +422,9 @@ __device__ __forceinline__ void split_store(u32x4 mine, char *base, uint32_t nre
 // source: aligned 28.2 / 185 us; offsets of which half are whole dwords 28.3 /
 // 186, every source 6 bytes off 34 / 222; reading aligned vectors and joining
 // neighbours' across lanes took 32.3 / 218.7 at any offsets, and the dword
-// below each vector with a lane shift of one dword 30 / 200).
+// below each vector with a lane shift of one dword 30 / 200; int8 at mixed byte
+// offsets 64 / 128 MiB 98 / 200 here and 97 / 187 joined across lanes, e4m3 98 / 200
+// and 118 / 230).
 template <int G, class Src>
 __device__ __forceinline__ void fetch_any(u32x4 (&v)[G], const Src &src, int p0, size_t at,
                                           uint32_t o)
@@ -546,8 +550,8 @@ constexpr int reduce_min_waves()
 // dst[i] = fold_p src_p[i] for lead + nvec*kVec + tail elements, every source
 // at the same offset within 16 bytes, dst too or (OFF) at another: the first
 // `lead` elements (fewer than a vector) bring the sources to a 16-byte boundary
-// and, like the last `tail` ones, are done by one workgroup, scalar; the nvec vectors
-// between go in tiles of B * U vectors (the last one ragged, cut by the buffer
+// and, like the last `tail` ones, are done by one workgroup, scalar; the nvec
+// vectors between go in tiles of B * U vectors (the last one ragged, cut by the buffer
 // range check).  `head` (a multiple of 16 below 128, at most nvec*16) is the
 // byte length of a first, short tile that ends where the first source
 // reaches a 128-byte line: the other tiles then start on line boundaries, so

@@ -15,37 +15,40 @@
 namespace xred {
 namespace {
 
-// Three tile shapes, one 16-byte vector of every source per thread but for the second:
+// Three tile shapes, one 16-byte vector of every source per thread but for the
+// second's up to 8 sources:
 //
 // * Up to 8 sources, launches of at most four 512-thread workgroups per CU (up
 //   to 8 MiB per source) are latency-bound: 512-thread workgroups, uncapped, so
 //   the whole message is in flight after the fewest workgroup dispatches (P=8
 //   bf16 4 MiB per source 6.8 us against 7.0-7.4 with 128 threads; equal at 7
 //   MiB; e4m3 8 MiB 11.2 / 12.3).  All four are resident at once where a kernel
-//   takes at most 64 VGPRs, as these do.  More sources spread over the chip in
+//   takes at most 64 VGPRs, as most do.  More sources spread over the chip in
 //   128-thread workgroups (P=32 bf16 1 / 4 / 7 MiB: 6.4 / 22.2 / 38.2 us against
 //   8.1 / 23.6 / 41.6; P=16 512 KiB 3.1 against 4.3), except in the next case.
 //   Counts without a kernel of their own keep the next group of 8 sources in
 //   flight up to 1 MiB a source, where few waves hide the loads (bf16, rotating
-//   buffers, with / without: P=9, 24, 48 512 KiB 3.6 / 3.8, 4.7 / 5.2, 7.2 / 8.3 us;
-//   P=9 32 MiB 54.6 / 51.2).
+//   buffers, with / without: P=9, 24, 48 512 KiB 3.6 / 3.8, 4.7 / 5.2, 7.2 / 8.3
+//   us; P=9 32 MiB 54.6 / 51.2).
 // * A call of at most 128 MiB of sources and output (half the MALL) mostly finds
 //   the last step's buffers there, and is then bound by dispatches and by what
 //   the wave cap keeps out rather than by HBM.  Up to the same number of
-//   workgroups, up to 8 sources take 512-thread ones of two vectors a thread while
-//   the call has at most 108 MiB, and more sources past 1 MiB each those of one,
-//   uncapped (bf16, this / 128-thread tiles: P=2 12 MiB 4.3 / 6.8 us, P=4 9 / 16 MiB
-//   7.3 / 8.2, 11.2 / 12.1, P=8 12 MiB 15.3 / 16.9, e4m3 16.5 / 17.5; P=9 4 MiB 5.6 /
-//   7.7, P=12 2 / 4 MiB 4.5 / 4.6, 7.8 / 8.5, P=16 2 / 4 MiB 5.2 / 5.4, 9.6 / 11.2,
-//   e4m3 P=16 4 MiB 10.9 / 12.1).  108 MiB is 12 MiB of 8 sources: there two vectors a thread make three whole workgroups per CU; at
-//   13 to 15 MiB, a broken fourth, the 128-thread tiles win warm and from HBM (two
-//   vectors / 128 threads, back to back and rotating buffers: 13 MiB 18.4 / 17.3,
-//   21.6 / 20.0 us; 14 MiB 19.9 / 19.2, 22.9 / 21.3; e4m3 13 MiB 19.4 / 18.1, 22.5 / 20.6).
-//   At 16 MiB it depends on the buffers' addresses: 16 MiB apart 22.3 / 23.6, 25.1 /
-//   24.3; with 4 KiB, 1 MiB or 2 MiB more between them 21.8 / 22.6, 22.4 / 21.0 and
-//   22.3 / 22.3 back to back, 24.4 / 24.6, 25.2 / 24.0 and 25.0 / 23.9 rotating.
-//   Outputs off the sources' grid keep two vectors to 128 MiB (P=8 14 MiB 20.8 / 21.5
-//   back to back; P=7 16 MiB 20.6 / 22.3).
+//   workgroups, up to 8 sources take 512-thread ones of two vectors a thread
+//   while the call has at most 108 MiB, and more sources past 1 MiB each those
+//   of one, uncapped (bf16, this / 128-thread tiles: P=2 12 MiB 4.3 / 6.8 us,
+//   P=4 9 / 16 MiB 7.3 / 8.2, 11.2 / 12.1, P=8 12 MiB 15.3 / 16.9, e4m3 16.5 /
+//   17.5; P=9 4 MiB 5.6 / 7.7, P=12 2 / 4 MiB 4.5 / 4.6, 7.8 / 8.5, P=16 2 / 4
+//   MiB 5.2 / 5.4, 9.6 / 11.2, e4m3 P=16 4 MiB 10.9 / 12.1).  108 MiB is 12 MiB
+//   of 8 sources: there two vectors a thread make three whole workgroups per CU;
+//   at 13 to 15 MiB, a broken fourth, the 128-thread tiles win warm and from HBM
+//   (two vectors / 128 threads, back to back and rotating buffers: 13 MiB 18.4 /
+//   17.3, 21.6 / 20.0 us; 14 MiB 19.9 / 19.2, 22.9 / 21.3; e4m3 13 MiB 19.4 /
+//   18.1, 22.5 / 20.6).  At 16 MiB it depends on the buffers' addresses: 16 MiB
+//   apart 22.3 / 23.6, 25.1 / 24.3; with 4 KiB, 1 MiB or 2 MiB more between them
+//   21.8 / 22.6, 22.4 / 21.0 and 22.3 / 22.3 back to back, 24.4 / 24.6, 25.2 /
+//   24.0 and 25.0 / 23.9 rotating.  Outputs off the sources' grid keep two
+//   vectors to 128 MiB (P=8 14 MiB 20.8 / 21.5 back to back; P=7 16 MiB 20.6 /
+//   22.3).
 // * Larger launches are bandwidth-bound: 128-thread workgroups with a
 //   bounded number of waves per CU.  HBM3E on MI355X delivers the most when
 //   a CU keeps a moderate number of loads in flight; more waves than that
@@ -58,12 +61,14 @@ namespace {
 //   wanted number of workgroups fit on a CU.
 // * Five to eight sources want more loads in flight when each holds several
 //   hundred MiB, and when a launch is only a few rounds long (12 / 16 / 20 / 24
-//   waves, back to back: P=5 bf16 17 MiB 16.7 / 15.3 / 15.1 / 15.1 us, 24 MiB 24.1 /
-//   23.2 / 23.1 / 23.0; P=6 24 MiB 27.9 / 26.7 / 26.8 / 26.8; P=7 24 MiB 29.5 / 28.2 / 28.2 /
-//   28.7; P=8 17 MiB 22.9 / 22.5 / 22.7 / 23.1, 24 MiB 33.3 / 33.5 / 33.6 / 33.9; P=8 e4m3
-//   17 MiB 25.0 / 23.7 / 23.4 / 23.8, int8 24 MiB 35.3 / 32.2 / 32.9 / 33.1, fp32 within 1 %
-//   of bf16); P=8 32 MiB and 128 MiB 12; 256 MiB 16, 360 us against 374 us; 512 MiB 24, 830 us against 963 us; 768 MiB 20-24,
-//   1232 us against 1346 us).  16 and 32 sources keep their caps up to 4.4 GB.
+//   waves, back to back: P=5 bf16 17 MiB 16.7 / 15.3 / 15.1 / 15.1 us, 24 MiB
+//   24.1 / 23.2 / 23.1 / 23.0; P=6 24 MiB 27.9 / 26.7 / 26.8 / 26.8; P=7 24 MiB
+//   29.5 / 28.2 / 28.2 / 28.7; P=8 17 MiB 22.9 / 22.5 / 22.7 / 23.1, 24 MiB 33.3
+//   / 33.5 / 33.6 / 33.9; P=8 e4m3 17 MiB 25.0 / 23.7 / 23.4 / 23.8, int8 24 MiB
+//   35.3 / 32.2 / 32.9 / 33.1, fp32 within 1 % of bf16); P=8 32 MiB and 128 MiB
+//   12; 256 MiB 16, 360 us against 374 us; 512 MiB 24, 830 us against 963 us;
+//   768 MiB 20-24, 1232 us against 1346 us).  16 and 32 sources keep their caps
+//   up to 4.4 GB.
 //
 // Tile order of the 128-thread shape.  In address order, with one 2 KiB tile
 // per workgroup, XCD x reads the 2 KiB blocks x mod 8 of every stream.  That is
@@ -76,7 +81,12 @@ namespace {
 // equal bases, 25.2 us with two vectors per 512-thread workgroup -> 23.5).
 // With equal bases address order wins from about 512 MiB of sources up (P=8
 // 64 MiB 87.4 against 86.9 in runs, 128 MiB 179.9 / 183.7; P=4 64 MiB 49.3 /
-// 48.8, 128 MiB 104.7 / 106.2; P=32 16 MiB 86.6 / 86.8, 32 MiB 169.3 / 173.4).
+// 48.8, 128 MiB 104.7 / 106.2; P=32 16 MiB 86.6 / 86.8, 32 MiB 169.3 / 173.4; int8
+// P=32 48 MiB 252 / 258, bf16 P=64 24 MiB 246 / 255).  Below it runs win in every
+// count and type (address order / runs, rotating buffers: P=2 24 / 64 MiB 13.9 /
+// 12.6, 31.5 / 29.3 us, P=3 24 MiB 17.9 / 15.8, P=6 64 MiB 72.3 / 68.4, P=12 24 MiB
+// 58.1 / 50.7, P=16 24 MiB 71.7 / 66.1, P=64 8 MiB 99.8 / 88.6; P=8 24 MiB fp32 40.3 /
+// 34.9, e4m3 40.0 / 35.6; int8 P=32 8 MiB 59.3 / 45.1).
 constexpr int kB = 128;        // threads per workgroup, bandwidth-bound launches
 constexpr int kBWide = 512;    // threads per workgroup, one-round launches
 constexpr int kWideWgsPerCu = 4;   // most 512-thread workgroups per CU of one-round launches
