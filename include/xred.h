@@ -70,8 +70,9 @@
  *     items shorter than a vector or two take a slower scalar path with the
  *     same results).
  *     xred_ring_reduce refuses chunks at different offsets (see there);
- *     xred_reduce_copy_step and xred_acc_cast run at one speed whatever the
- *     buffers' alignment; xred_allreduce_sim takes the vector path only when
+ *     xred_reduce_copy_step and xred_acc_cast read and write in vectors at any
+ *     element alignment (outputs of 8- and 16-bit types a little slower where
+ *     they are not 4-byte aligned); xred_allreduce_sim takes the vector path only when
  *     every buffer it touches is 16-byte aligned, else a scalar one.
  *   - Device words the library binds to a stream (the ring's relay word, the
  *     batch queue's counters) are looked up by the stream's handle.  Let a
