@@ -24,6 +24,8 @@
 
 #pragma once
 
+#include <type_traits>
+
 #include "xred_dispatch.hpp"
 #include "xred_internal.hpp"
 #include "xred_kernels.hpp"
@@ -202,33 +204,42 @@ __device__ __forceinline__ void run_tile(const TileDesc &d, Mid &&mid)
                            d.lead + nvec * T::kVec, EARLY ? threadIdx.x - (kB - 64) : threadIdx.x);
     };
     if (d.path == kGrid) {
-        // groups of 8 sources; sources beyond nsrc get an empty buffer range
+        // Groups of 8 sources.  A source the item does not have is not read: a
+        // load of an empty range still takes its turn in the address units (P=1:
+        // range kernel 2070 us a 9.7 GB batch, 2310 with them; 100 items of 4 MiB
+        // captured 201 / 281 us, with P=2 231 / 294; 1000 log-uniform eager 115 /
+        // 166; P=9 159 / 170).  A whole first group has no test per source, which
+        // gains over one body with them (captured P=8 4096 items 904 / 935 us).
         const uint32_t nrec = toff < vbytes ? tile_nrec(vbytes, toff, kBytes) : 0u;
         u32x4 in[8][SUB];
         typename T::Acc acc[SUB][T::kVec];
-        auto load = [&](int q, const char *p, bool on) {
-            const rsrc_t r = make_rsrc((on ? p : d.dst) + lb + toff, on ? nrec : 0u);
+        auto load = [&](int q, const char *p) {
+            const rsrc_t r = make_rsrc(p + lb + toff, nrec);
 #pragma unroll
             for (int h = 0; h < SUB; ++h)
                 in[q][h] = bload<kLoadStream>(r, (uint32_t)(h * kB + threadIdx.x) * 16u);
         };
+        auto first = [&](auto whole) {
+            constexpr bool kWhole = decltype(whole)::value;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) load(q, d.p[q], q < d.nsrc);
-        mid();
-        if (EARLY) ends();
+            for (int q = 0; q < 8; ++q)
+                if (kWhole || q < d.nsrc) load(q, d.p[q]);
+            mid();
+            if (EARLY) ends();
 #pragma unroll
-        for (int h = 0; h < SUB; ++h) {
-            up_vec<T>(in[0][h], acc[h]);
+            for (int h = 0; h < SUB; ++h) {
+                up_vec<T>(in[0][h], acc[h]);
 #pragma unroll
-            for (int q = 1; q < 8; ++q)
-                if (q < d.nsrc) fold_vec<T, Op>(acc[h], in[q][h]);
-        }
+                for (int q = 1; q < 8; ++q)
+                    if (kWhole || q < d.nsrc) fold_vec<T, Op>(acc[h], in[q][h]);
+            }
+        };
+        if (d.nsrc >= 8) first(std::true_type{});
+        else first(std::false_type{});
         for (int p0 = 8; p0 < d.nsrc; p0 += 8) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool on = p0 + q < d.nsrc;
-                load(q, sload(d.srcs + (on ? p0 + q : 0)), on);
-            }
+            for (int q = 0; q < 8; ++q)
+                if (p0 + q < d.nsrc) load(q, sload(d.srcs + p0 + q));
 #pragma unroll
             for (int h = 0; h < SUB; ++h)
 #pragma unroll
