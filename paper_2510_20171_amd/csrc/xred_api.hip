@@ -618,8 +618,8 @@ unsigned batched_device_grid()
 // A batch of one run binds no slot: the first launch that does allocates and
 // waits for its stream, and a slot follows a stream's handle.  It is the
 // faster one too until the items are large (bf16 log-uniform to 1 MiB, runs /
-// queue: 16 items of P=2 6.6 / 8.4 us, 32 of P=8 13.1 / 16.6, 48 of P=4 9.1 /
-// 13.3, 64 of P=8 24.2 / 26.4; 64 of 1 MiB 105.7 / 100.8, 64 of 8 MiB 857 / 760).
+// queue: 16 items of P=2 7.1 / 7.4 us, 32 of P=8 12.3 / 17.0, 48 of P=4 11.9 /
+// 16.6, 64 of P=8 21.3 / 24.9; 64 of 1 MiB 104.4 / 100.8, 64 of 8 MiB 847 / 760).
 hipError_t batched_device(const xred_item *items, int nitems, xred_dtype dtype, xred_op op,
                           hipStream_t stream)
 {

@@ -206,7 +206,7 @@ __device__ __forceinline__ void run_tile(const TileDesc &d, Mid &&mid)
     if (d.path == kGrid) {
         // Groups of 8 sources.  A source the item does not have is not read: a
         // load of an empty range still takes its turn in the address units (P=1:
-        // range kernel 2070 us a 9.7 GB batch, 2310 with them; 100 items of 4 MiB
+        // range kernel 2070 us a 10.2 GB batch, 2310 with them; 100 items of 4 MiB
         // captured 201 / 281 us, with P=2 231 / 294; 1000 log-uniform eager 115 /
         // 166; P=9 159 / 170).  A whole first group has no test per source, which
         // gains over one body with them (captured P=8 4096 items 904 / 935 us).
